@@ -1,4 +1,4 @@
-// The C ABI (include/gmm.h): validation, state ownership, dispatch, state I/O.
+// The C ABI (include/gmm.h): validation, state ownership, dispatch, state snapshots.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -6,7 +6,6 @@
 #include <cstring>
 #include <new>
 #include <string>
-#include <vector>
 
 #include "gmm.h"
 #include "gmm_internal.hpp"
@@ -27,76 +26,6 @@ gmm_status hip_fail(hipError_t e, const char* what) {
 }
 
 static inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
-
-// Round a double to a binary format with `p` significant bits and smallest normal exponent
-// `emin`, to nearest with ties to even; returns the rounded value as a double.
-static double round_to_format(double v, int p, int emin, double maxv) {
-  if (v == 0.0 || !std::isfinite(v)) return v;
-  int e = 0;
-  (void)std::frexp(v, &e);  // |v| in [2^(e-1), 2^e)
-  const int qexp = std::max(e - p, emin - p + 1);
-  double r = std::ldexp(std::nearbyint(std::ldexp(v, -qexp)), qexp);
-  if (std::fabs(r) > maxv) r = std::copysign(INFINITY, r);
-  return r;
-}
-
-static uint16_t half_bits_exact(double r) {  // r exactly representable as binary16
-  uint16_t sign = std::signbit(r) ? 0x8000u : 0u;
-  double a = std::fabs(r);
-  if (a == 0.0) return sign;
-  if (std::isinf(a)) return sign | 0x7C00u;
-  int e = std::ilogb(a);
-  if (e >= -14) {
-    const uint16_t mant = static_cast<uint16_t>(std::ldexp(a, -e) * 1024.0 - 1024.0);
-    return sign | static_cast<uint16_t>((e + 15) << 10) | mant;
-  }
-  return sign | static_cast<uint16_t>(std::ldexp(a, 24));
-}
-
-static double half_value(uint16_t h) {
-  const double s = (h & 0x8000u) ? -1.0 : 1.0;
-  const int ex = (h >> 10) & 0x1F;
-  const int m = h & 0x3FF;
-  if (ex == 0) return s * std::ldexp(static_cast<double>(m), -24);
-  if (ex == 31) return m ? NAN : s * INFINITY;
-  return s * std::ldexp(1024.0 + m, ex - 25);
-}
-
-static void pack_values(const double* in, void* out, size_t n, int dtype) {
-  if (dtype == GMM_F32) {
-    float* o = static_cast<float*>(out);
-    for (size_t i = 0; i < n; ++i) o[i] = static_cast<float>(in[i]);  // round to nearest even
-  } else if (dtype == GMM_F16) {
-    uint16_t* o = static_cast<uint16_t*>(out);
-    for (size_t i = 0; i < n; ++i) o[i] = half_bits_exact(round_to_format(in[i], 11, -14, 65504.0));
-  } else {
-    uint16_t* o = static_cast<uint16_t*>(out);
-    for (size_t i = 0; i < n; ++i) {
-      const float f = static_cast<float>(round_to_format(in[i], 8, -126, 3.3895313892515355e38));
-      uint32_t u;
-      std::memcpy(&u, &f, 4);
-      o[i] = static_cast<uint16_t>(u >> 16);
-    }
-  }
-}
-
-static void unpack_values(const void* in, double* out, size_t n, int dtype) {
-  if (dtype == GMM_F32) {
-    const float* s = static_cast<const float*>(in);
-    for (size_t i = 0; i < n; ++i) out[i] = s[i];
-  } else if (dtype == GMM_F16) {
-    const uint16_t* s = static_cast<const uint16_t*>(in);
-    for (size_t i = 0; i < n; ++i) out[i] = half_value(s[i]);
-  } else {
-    const uint16_t* s = static_cast<const uint16_t*>(in);
-    for (size_t i = 0; i < n; ++i) {
-      const uint32_t u = static_cast<uint32_t>(s[i]) << 16;
-      float f;
-      std::memcpy(&f, &u, 4);
-      out[i] = f;
-    }
-  }
-}
 
 }  // namespace rgbd
 
@@ -469,136 +398,6 @@ gmm_status gmm_apply_frame_augmented(gmm_handle* h, const uint8_t* rgb, int64_t 
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, kModeAug, streams_state(h), s);
   if (e != hipSuccess) return hip_fail(e, "augmented frame kernel launch");
-  h->last_stream = s;
-  return GMM_OK;
-}
-
-gmm_status gmm_read_state(gmm_handle* h, double* host_out, void* stream) {
-  if (!h || !host_out) return fail(GMM_ERR_INVALID_ARG, "NULL argument");
-  DeviceGuard g(h->cfg.device);
-  if (!g.ok()) return fail(GMM_ERR_DEVICE, "cannot select the handle's device");
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t total = h->rgb_bytes + h->depth_bytes + h->fuse_bytes;
-  std::vector<uint8_t> raw;
-  try {
-    raw.resize(total);
-  } catch (...) {
-    return fail(GMM_ERR_OUT_OF_MEMORY, "host staging buffer");
-  }
-  hipError_t e = hipMemcpyAsync(raw.data(), h->mem, total, hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return hip_fail(e, "state copy to host");
-  const size_t n = static_cast<size_t>(h->npix), M = static_cast<size_t>(h->cfg.M);
-  double* o = host_out;
-  size_t off = 0;
-  for (int blk = 0; blk < 2; ++blk) {
-    const bool present = blk == 0 ? has_rgb(h) : sep_depth(h);
-    if (!present) continue;
-    const size_t P = blk == 0 ? (is_augmented(h) ? 6 : 5) : 3;
-    const uint32_t C = static_cast<uint32_t>(P - 2);
-    const uint32_t es = static_cast<uint32_t>(h->esize);
-    // scaled weights: the weight is the pixel's effective scale (the tile's scale times the
-    // pixel's hole factor, one fp32 product as the kernels form it) times the scaled weight (a
-    // product of two floats, exact in double)
-    const uint8_t* flags = sep_depth(h) ? raw.data() + h->rgb_bytes + h->depth_bytes : nullptr;
-    const rgbd::ModelConsts& kcon = blk == 0 ? h->kc : h->kd;
-    std::vector<double> scale;
-    if (scaled_weights(es)) {
-      try {
-        scale.resize(h->tiles64);
-      } catch (...) {
-        return fail(GMM_ERR_OUT_OF_MEMORY, "host staging buffer");
-      }
-      for (size_t t = 0; t < h->tiles64; ++t)
-        unpack_values(raw.data() + off + state_scale_offset(t, h->tiles64, static_cast<uint32_t>(M), C, es),
-                      &scale[t], 1, h->cfg.state_dtype);
-    }
-    // two-plane device layout -> canonical [param][rank][pixel]
-    for (size_t k = 0; k < P * M; ++k) {
-      const uint32_t param = static_cast<uint32_t>(k / M);
-      const uint32_t v = value_index(param, static_cast<uint32_t>(k % M), static_cast<uint32_t>(M), C, es);
-      for (size_t i = 0; i < n; ++i) {
-        const size_t at = off + state_value_offset(v, i, h->tiles64, static_cast<uint32_t>(M), C, es);
-        unpack_values(raw.data() + at, o + i, 1, h->cfg.state_dtype);
-        if (param == C + 1 && !scale.empty()) {
-          float gi = static_cast<float>(scale[i / kWave]);
-          if (blk == 1 && flags) gi = gi * hole_factor(flags[i] >> kHoleShift, kcon.dk);
-          o[i] *= static_cast<double>(gi);
-        }
-      }
-      o += n;
-    }
-    off += blk == 0 ? h->rgb_bytes : h->depth_bytes;
-  }
-  if (sep_both(h)) {
-    const uint8_t* f = raw.data() + off;
-    for (size_t i = 0; i < n; ++i) o[i] = static_cast<double>((f[i] >> 3) & 1u);
-    o += n;
-    for (size_t i = 0; i < n; ++i) o[i] = static_cast<double>(static_cast<int>(f[i] & 7u) - 3);
-  }
-  return GMM_OK;
-}
-
-gmm_status gmm_write_state(gmm_handle* h, const double* host_in, void* stream) {
-  if (!h || !host_in) return fail(GMM_ERR_INVALID_ARG, "NULL argument");
-  const size_t n = static_cast<size_t>(h->npix), M = static_cast<size_t>(h->cfg.M);
-  const size_t total = h->rgb_bytes + h->depth_bytes + h->fuse_bytes;
-  std::vector<uint8_t> raw;
-  try {
-    raw.assign(total, 0);
-  } catch (...) {
-    return fail(GMM_ERR_OUT_OF_MEMORY, "host staging buffer");
-  }
-  const double* in = host_in;
-  size_t off = 0;
-  for (int blk = 0; blk < 2; ++blk) {
-    const bool present = blk == 0 ? has_rgb(h) : sep_depth(h);
-    if (!present) continue;
-    const size_t P = blk == 0 ? (is_augmented(h) ? 6 : 5) : 3;
-    const uint32_t C = static_cast<uint32_t>(P - 2);
-    const uint32_t es = static_cast<uint32_t>(h->esize);
-    // scaled weights are written with scale 1 (rank 1's key is computed on the device below)
-    if (scaled_weights(es)) {
-      const double one = 1.0;
-      for (size_t t = 0; t < h->tiles64; ++t)
-        pack_values(&one, raw.data() + off + state_scale_offset(t, h->tiles64, static_cast<uint32_t>(M), C, es), 1,
-                    h->cfg.state_dtype);
-    }
-    // canonical [param][rank][pixel] -> two-plane device layout
-    for (size_t k = 0; k < P * M; ++k) {
-      const uint32_t v = value_index(static_cast<uint32_t>(k / M), static_cast<uint32_t>(k % M),
-                                     static_cast<uint32_t>(M), C, es);
-      for (size_t i = 0; i < n; ++i) {
-        const size_t at = off + state_value_offset(v, i, h->tiles64, static_cast<uint32_t>(M), C, es);
-        pack_values(in + i, raw.data() + at, 1, h->cfg.state_dtype);
-      }
-      in += n;
-    }
-    off += blk == 0 ? h->rgb_bytes : h->depth_bytes;
-  }
-  if (sep_both(h)) {
-    uint8_t* f = raw.data() + off;
-    for (size_t i = 0; i < n; ++i) {
-      const double I = in[i], c = in[n + i];
-      if (!(I == 0.0 || I == 1.0)) return fail(GMM_ERR_INVALID_ARG, "fusion bit I must be 0 or 1");
-      if (!(c == std::floor(c) && c >= -3.0 && c <= 3.0))
-        return fail(GMM_ERR_INVALID_ARG, "fusion counter cpt must be an integer in [-3, 3]");
-      f[i] = static_cast<uint8_t>((static_cast<int>(c) + 3) | (static_cast<int>(I) << 3));
-    }
-    for (size_t i = n; i < h->fuse_bytes; ++i) f[i] = static_cast<uint8_t>(kFuseInit);
-  } else if (sep_depth(h)) {  // the flags bytes of a depth-only handle: no List 1 state, no holes counted
-    uint8_t* f = raw.data() + off;
-    for (size_t i = 0; i < h->fuse_bytes; ++i) f[i] = static_cast<uint8_t>(kFuseInit);
-  }
-  DeviceGuard g(h->cfg.device);
-  if (!g.ok()) return fail(GMM_ERR_DEVICE, "cannot select the handle's device");
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = hipMemcpyAsync(h->mem, raw.data(), total, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess && has_rgb(h))
-    e = launch_rekey(h->st_rgb, h->cfg.state_dtype, h->tiles64, h->cfg.M, is_augmented(h) ? 4 : 3, s);
-  if (e == hipSuccess && sep_depth(h)) e = launch_rekey(h->st_depth, h->cfg.state_dtype, h->tiles64, h->cfg.M, 1, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return hip_fail(e, "state copy to device");
   h->last_stream = s;
   return GMM_OK;
 }
