@@ -224,7 +224,7 @@ gmm_status gmm_write_state(gmm_handle* h, const double* host_in, void* stream);
 gmm_status gmm_state_save(gmm_handle* h, void* device_dst, void* stream);
 gmm_status gmm_state_restore(gmm_handle* h, const void* device_src, void* stream);
 
-/* ---- batched path: many streams, one persistent launch per frame-set --------------------- */
+/* ---- batched path: many streams, one launch per frame-set -------------------------------- */
 
 typedef struct gmm_batch gmm_batch;
 
@@ -241,9 +241,11 @@ typedef struct {
   uint64_t* fused;
 } gmm_stream_io;
 
-/* Launch shape of the persistent kernel: threads per block (256 or 512), pixels per tile (a
- * multiple of block_threads, at most 64x it; a tile never spans two streams) and resident
- * blocks per compute unit (1..32; grid = blocks_per_cu x CU count, capped at the tile count). */
+/* Launch shape of the batched kernel: threads per block (256 or 512), pixels per tile (a multiple
+ * of block_threads, at most 64x it; a tile never spans two streams) and blocks per compute unit
+ * (1..32): grid = blocks_per_cu x CU count, capped at the tile count, each block walking tiles;
+ * where blocks_per_cu x block_threads is 2048 or more, all a CU holds, one block per tile. A
+ * launch with the default shape, none having been set or found, may cut tiles into smaller pieces. */
 typedef struct {
   int32_t block_threads;
   int32_t tile_pixels;
@@ -277,7 +279,7 @@ gmm_status gmm_batch_set_frames(gmm_batch* b, int32_t slot, const gmm_stream_io*
 
 /*
  * Advance every stream of the batch one frame using the frames and masks of slot `slot`, in one
- * persistent launch on `stream`. Per stream, results (masks and state) are bit-identical to
+ * launch on `stream`. Per stream, results (masks and state) are bit-identical to
  * gmm_apply_frame (or gmm_apply_frame_fused when `fused` was given). Allocates nothing and does
  * not synchronise: safe to capture in a hipGraph.
  */

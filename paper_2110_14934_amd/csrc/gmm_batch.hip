@@ -1,14 +1,14 @@
-// Batched path: every stream of a batch advances one frame in ONE persistent launch.
+// Batched path: every stream of a batch advances one frame in ONE launch.
 //
 // Work is cut into tiles of `tile_pixels` consecutive pixels of one stream (a multiple of the
-// block size, so tiles start on mask-word boundaries). A device tile map gives each tile's
-// stream; per-stream kernel arguments (frame and mask pointers, state blocks, constants) live in
-// a device descriptor table with one slot per prepared frame-set. The grid is a multiple of the
-// CU count and each block walks tiles b, b+G, b+2G, ... so every block samples every stream and
-// uneven resolutions balance without atomics. The per-pixel body is the one the single-stream
-// kernel uses (process_pixel), so results are bit-identical to one launch per stream.
+// block size, so tiles start on mask-word boundaries). Per-stream kernel arguments (frame and mask
+// pointers, state blocks, constants) live in a device descriptor table with one slot per prepared
+// frame-set, each stream's first tile in an array beside it that a block searches for the stream
+// of its tile. The per-pixel body is the one
+// the single-stream kernel uses (process_pixel), so results are bit-identical to one launch per
+// stream.
 //
-// A launch reads only device memory prepared earlier (descriptor slot, tile map): it allocates
+// A launch reads only device memory prepared earlier (descriptor slot, first tiles): it allocates
 // nothing and synchronises nothing, so it can be captured into a hipGraph and replayed.
 #include <hip/hip_runtime.h>
 
@@ -28,68 +28,105 @@
 
 namespace rgbd {
 
+// The stream of tile t: the last entry of `first` (n entries, first[0] = 0, increasing) that is
+// <= t. A binary search in scalar registers: its loads hit the scalar cache that every block of
+// the CU reads `first` through, which a tile map of one word per tile does not (64 streams, fp32:
+// 312 us per launch either way), and a wave-wide probe of all entries at once, one vector load,
+// waits longer (321 us).
+__device__ __forceinline__ uint32_t find_stream(const uint32_t* __restrict__ first, uint32_t n, uint32_t t) {
+  uint32_t lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi + 1) >> 1;
+    if (first[mid] <= t) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
 // Five waves per SIMD: the body fits them without spilling (checked at build time by the tests).
+// A block takes one piece of a tile (tile_px >> piece_shift pixels) and the grid usually has a
+// block for every piece (batch_launch below); a smaller grid walks the pieces b, b+G, b+2G, ...
 // MEASURE: the body that adds each wave's state bytes to the streams' traffic records; the launch
 // takes it only when a stream of the batch has one, so the common body never forms the counts.
 template <int M, typename S, int BLOCK, bool MEASURE>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5))) batch_kernel(const FrameArgs* __restrict__ table,
-                                                      const uint32_t* __restrict__ tile_map,
-                                                      const uint32_t* __restrict__ first_tile,
-                                                      uint32_t n_tiles, uint32_t tile_px) {
+                                                      const uint32_t* __restrict__ first, uint32_t n_streams,
+                                                      uint32_t n_pieces, uint32_t tile_px, uint32_t piece_shift) {
   __shared__ uint32_t lds[BLOCK / kWave][48];
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = threadIdx.x / kWave;
-  for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-    const uint32_t s = tile_map[t];
+  const uint32_t piece_px = tile_px >> piece_shift, part_mask = (1u << piece_shift) - 1u;
+  for (uint32_t b = blockIdx.x; b < n_pieces; b += gridDim.x) {
+    const uint32_t t = b >> piece_shift;
+    const uint32_t s = find_stream(first, n_streams, t);
     const FrameArgs a = table[s];
-    const uint32_t t0 = (t - first_tile[s]) * tile_px;
-    process_tile<M, S, BLOCK, MEASURE>(a, t0, tile_px, lane, lds[wv]);
+    const uint32_t t0 = (t - first[s]) * tile_px + (b & part_mask) * piece_px;
+    process_tile<M, S, BLOCK, MEASURE>(a, t0, piece_px, lane, lds[wv]);
   }
 }
 
 template <int M, typename S, bool MEASURE>
-static hipError_t launch_batch_msm(int block, dim3 grid, const FrameArgs* table, const uint32_t* map,
-                                   const uint32_t* first, uint32_t n_tiles, uint32_t tile_px, hipStream_t s) {
-  if (block == 256)
-    batch_kernel<M, S, 256, MEASURE><<<grid, dim3(256), 0, s>>>(table, map, first, n_tiles, tile_px);
-  else if (block == 512)
-    batch_kernel<M, S, 512, MEASURE><<<grid, dim3(512), 0, s>>>(table, map, first, n_tiles, tile_px);
+static hipError_t launch_batch_msm(const BatchLaunch& l, hipStream_t s) {
+  const dim3 grid(l.grid);
+  if (l.block == 256)
+    batch_kernel<M, S, 256, MEASURE><<<grid, dim3(256), 0, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
+  else if (l.block == 512)
+    batch_kernel<M, S, 512, MEASURE><<<grid, dim3(512), 0, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 template <int M, typename S>
-static hipError_t launch_batch_ms(int block, dim3 grid, const FrameArgs* table, const uint32_t* map,
-                                  const uint32_t* first, uint32_t n_tiles, uint32_t tile_px, bool measure,
-                                  hipStream_t s) {
-  return measure ? launch_batch_msm<M, S, true>(block, grid, table, map, first, n_tiles, tile_px, s)
-                 : launch_batch_msm<M, S, false>(block, grid, table, map, first, n_tiles, tile_px, s);
+static hipError_t launch_batch_ms(const BatchLaunch& l, hipStream_t s) {
+  return l.measure ? launch_batch_msm<M, S, true>(l, s) : launch_batch_msm<M, S, false>(l, s);
 }
 
 template <typename S>
-static hipError_t launch_batch_s(int M, int block, dim3 grid, const FrameArgs* table, const uint32_t* map,
-                                 const uint32_t* first, uint32_t n_tiles, uint32_t tile_px, bool measure,
-                                 hipStream_t s) {
+static hipError_t launch_batch_s(int M, const BatchLaunch& l, hipStream_t s) {
   switch (M) {
-    case 1: return launch_batch_ms<1, S>(block, grid, table, map, first, n_tiles, tile_px, measure, s);
-    case 2: return launch_batch_ms<2, S>(block, grid, table, map, first, n_tiles, tile_px, measure, s);
-    case 3: return launch_batch_ms<3, S>(block, grid, table, map, first, n_tiles, tile_px, measure, s);
-    case 4: return launch_batch_ms<4, S>(block, grid, table, map, first, n_tiles, tile_px, measure, s);
-    case 5: return launch_batch_ms<5, S>(block, grid, table, map, first, n_tiles, tile_px, measure, s);
+    case 1: return launch_batch_ms<1, S>(l, s);
+    case 2: return launch_batch_ms<2, S>(l, s);
+    case 3: return launch_batch_ms<3, S>(l, s);
+    case 4: return launch_batch_ms<4, S>(l, s);
+    case 5: return launch_batch_ms<5, S>(l, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_batch(int M, int dtype, int block, dim3 grid, const FrameArgs* table,
-                               const uint32_t* map, const uint32_t* first, uint32_t n_tiles,
-                               uint32_t tile_px, bool measure, hipStream_t s) {
+hipError_t launch_batch(int M, int dtype, const BatchLaunch& l, hipStream_t s) {
   switch (dtype) {
-    case GMM_F32: return launch_batch_s<float>(M, block, grid, table, map, first, n_tiles, tile_px, measure, s);
-    case GMM_F16: return launch_batch_s<f16s>(M, block, grid, table, map, first, n_tiles, tile_px, measure, s);
-    case GMM_BF16: return launch_batch_s<bf16s>(M, block, grid, table, map, first, n_tiles, tile_px, measure, s);
+    case GMM_F32: return launch_batch_s<float>(M, l, s);
+    case GMM_F16: return launch_batch_s<f16s>(M, l, s);
+    case GMM_BF16: return launch_batch_s<bf16s>(M, l, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+// Grid: with as many blocks per CU as a CU can hold (2048 threads) or more, one block per piece:
+// the dispatcher then hands the next piece to whichever CU is free, where blocks walking fixed
+// pieces wait for the slowest (64 uneven fp32 streams, M = 5: 360 us walking 1024-pixel tiles with 8 blocks per
+// CU, 315 us one block per tile). Fewer blocks per CU walk.
+// Pieces: a launch whose shape the caller left open cuts the default tiles of 1024 pixels into
+// pieces of 512, or of 256 when all pixels together are few (kSmallBatchPixels): larger pieces
+// spread a block's start (the search, the descriptor) over more pixels, smaller ones leave a
+// shorter chain in each wave and an evener end. Pieces of 256 / 512 / 1024 pixels: 64 uneven fp32
+// streams (29 M pixels) 338 / 312 / 318 us, 32 VGA fp16 streams (9.8 M pixels) 145 / 140 / 147
+// us, 4 VGA fp32 streams (1.2 M) 25.1 / 23.9 / 27.1 us, 24 small fp32 streams (M = 3, 0.9 M)
+// 18.2 / 19.4 / 19.9 us, 2 fp32 streams of 320x240 (0.15 M) 8.4 / 9.6 / 13.6 us.
+constexpr uint64_t kSmallBatchPixels = uint64_t(1) << 20;
+constexpr uint32_t kMaxGrid = 1u << 22;  // blocks, so that grid x block stays below 2^32 threads
+
+BatchLaunch batch_launch(const gmm_batch_tuning& t, bool open, uint32_t n_tiles, uint64_t pixels, int cu_count) {
+  BatchLaunch l{};
+  l.block = t.block_threads;
+  l.tile_px = static_cast<uint32_t>(t.tile_pixels);
+  l.piece_shift = !open || n_tiles >= (1u << 28) ? 0u : (pixels < kSmallBatchPixels ? 2u : 1u);
+  l.n_pieces = n_tiles << l.piece_shift;
+  const bool walk = t.blocks_per_cu * t.block_threads < 2048;
+  const uint32_t want = walk ? static_cast<uint32_t>(t.blocks_per_cu) * static_cast<uint32_t>(cu_count) : kMaxGrid;
+  l.grid = std::max(1u, std::min(want, l.n_pieces));
+  return l;
 }
 
 // Tunings found by the autotuner, per (device, M, dtype, stream mix), for this process.
@@ -112,11 +149,11 @@ struct gmm_batch {
   std::vector<hipEvent_t> staging_done;      // last upload from each staging buffer
   std::vector<uint8_t> slot_ready;
   std::vector<uint8_t> slot_measure;         // a stream of the slot's descriptors has a traffic record
-  uint32_t* d_tile_map = nullptr;
-  size_t tile_map_cap = 0;
   uint32_t* d_first_tile = nullptr;
   uint32_t n_tiles = 0;
-  gmm_batch_tuning tuning{256, 1024, 8};
+  uint64_t pixels = 0;                       // of one frame of every stream
+  gmm_batch_tuning tuning = kDefaultTuning;
+  bool shape_open = true;                    // no launch shape set or found: batch_launch may cut the tiles
   hipStream_t last_stream = nullptr;
 };
 
@@ -133,33 +170,19 @@ static gmm_status validate_tuning(const gmm_batch_tuning* t) {
   return GMM_OK;
 }
 
-// Rebuild the tile map for tile size `tile_px` (synchronous; not for use under capture).
+// First tiles for tile size `tile_px` (synchronous; not for use under capture).
 static gmm_status build_tiles(gmm_batch* b, uint32_t tile_px) {
   std::vector<uint32_t> first(n_streams(b));
   uint64_t total = 0;
+  b->pixels = 0;
   for (size_t i = 0; i < n_streams(b); ++i) {
     first[i] = static_cast<uint32_t>(total);
     total += (static_cast<uint64_t>(b->handles[i]->npix) + tile_px - 1) / tile_px;
+    b->pixels += static_cast<uint64_t>(b->handles[i]->npix);
   }
   if (total >= (1ull << 31)) return fail(GMM_ERR_INVALID_ARG, "too many tiles in one batch");
-  std::vector<uint32_t> map(total);
-  for (size_t i = 0; i < n_streams(b); ++i) {
-    const uint32_t end = i + 1 < n_streams(b) ? first[i + 1] : static_cast<uint32_t>(total);
-    std::fill(map.begin() + first[i], map.begin() + end, static_cast<uint32_t>(i));
-  }
-  hipError_t e = hipSuccess;
-  if (total > b->tile_map_cap) {
-    if (b->d_tile_map) (void)hipFree(b->d_tile_map);
-    b->d_tile_map = nullptr;
-    b->tile_map_cap = 0;
-    e = hipMalloc(&b->d_tile_map, total * sizeof(uint32_t));
-    if (e != hipSuccess) return fail(GMM_ERR_OUT_OF_MEMORY, "tile map allocation failed");
-    b->tile_map_cap = total;
-  }
-  e = hipMemcpy(b->d_tile_map, map.data(), total * sizeof(uint32_t), hipMemcpyHostToDevice);
-  if (e == hipSuccess)
-    e = hipMemcpy(b->d_first_tile, first.data(), first.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
-  if (e != hipSuccess) return hip_fail(e, "tile map upload");
+  const hipError_t e = hipMemcpy(b->d_first_tile, first.data(), first.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+  if (e != hipSuccess) return hip_fail(e, "first tile upload");
   b->n_tiles = static_cast<uint32_t>(total);
   return GMM_OK;
 }
@@ -170,15 +193,17 @@ static gmm_status apply_tuning(gmm_batch* b, const gmm_batch_tuning& t) {
     if (st != GMM_OK) return st;
   }
   b->tuning = t;
+  b->shape_open = false;
   return GMM_OK;
 }
 
 static hipError_t run_slot(gmm_batch* b, int slot, hipStream_t s) {
-  const uint32_t want = static_cast<uint32_t>(b->tuning.blocks_per_cu) * static_cast<uint32_t>(b->cu_count);
-  const dim3 grid(std::max(1u, std::min(want, b->n_tiles)));
-  return launch_batch(b->M, b->dtype, b->tuning.block_threads, grid, b->d_table + static_cast<size_t>(slot) * n_streams(b),
-                      b->d_tile_map, b->d_first_tile, b->n_tiles, static_cast<uint32_t>(b->tuning.tile_pixels),
-                      b->slot_measure[slot] != 0, s);
+  BatchLaunch l = batch_launch(b->tuning, b->shape_open, b->n_tiles, b->pixels, b->cu_count);
+  l.table = b->d_table + static_cast<size_t>(slot) * n_streams(b);
+  l.first = b->d_first_tile;
+  l.n_streams = static_cast<uint32_t>(n_streams(b));
+  l.measure = b->slot_measure[slot] != 0;
+  return launch_batch(b->M, b->dtype, l, s);
 }
 
 static void free_batch(gmm_batch* b) {
@@ -187,7 +212,6 @@ static void free_batch(gmm_batch* b) {
   for (auto ev : b->staging_done)
     if (ev) (void)hipEventDestroy(ev);
   if (b->d_table) (void)hipFree(b->d_table);
-  if (b->d_tile_map) (void)hipFree(b->d_tile_map);
   if (b->d_first_tile) (void)hipFree(b->d_first_tile);
   delete b;
 }
@@ -291,7 +315,7 @@ gmm_status gmm_batch_set_tuning(gmm_batch* b, const gmm_batch_tuning* t) {
   if (st != GMM_OK) return st;
   DeviceGuard g(b->device);
   if (!g.ok()) return fail(GMM_ERR_DEVICE, "cannot select the batch's device");
-  (void)hipStreamSynchronize(b->last_stream);  // the tile map may be rebuilt
+  (void)hipStreamSynchronize(b->last_stream);  // the first tiles may be rebuilt
   return apply_tuning(b, *t);
 }
 

@@ -4,8 +4,7 @@
 // Per tick, HIP streams form the pipeline of the paper's Fig. 4(a): the frames of tick N+1 are
 // copied host->device while tick N is computed and the masks of tick N-1 are copied back.
 // Within a tick: host->device frame copies (spread over four copy-in streams, so several DMA
-// engines share the host link) -> descriptor upload, a
-// device-built tile map and one persistent batched launch (compute stream) -> mask copies
+// engines share the host link) -> descriptor upload and one batched launch (compute stream) -> mask copies
 // device->host (copy-out stream). A ring of `ring` tick slots bounds the work in flight; a
 // completion thread waits on each tick's last event in order and records its completion time.
 #include <hip/hip_runtime.h>
@@ -23,26 +22,9 @@
 #include <vector>
 
 #include "gmm.h"
-#include "gmm_frame.hpp"
 #include "gmm_internal.hpp"
 
 namespace rgbd {
-
-// tile_map[t] = the entry e with first[e] <= t < first[e + 1] (first has n + 1 entries)
-__global__ void __launch_bounds__(kBlock) tile_map_kernel(const uint32_t* __restrict__ first, uint32_t n,
-                                                         uint32_t* __restrict__ tile_map) {
-  const uint32_t t = blockIdx.x * kBlock + threadIdx.x;
-  if (t >= first[n]) return;
-  uint32_t lo = 0, hi = n;  // invariant: first[lo] <= t < first[hi]
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) / 2;
-    if (first[mid] <= t)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  tile_map[t] = lo;
-}
 
 static double now_s() {
   using namespace std::chrono;
@@ -90,12 +72,10 @@ constexpr int kCopyInStreams = 4;  // host->device copies spread over several DM
 struct Slot {
   hipEvent_t h2d_done[kCopyInStreams] = {};
   hipEvent_t compute_done = nullptr, done = nullptr;
-  FrameArgs* h_table = nullptr;   // pinned: n FrameArgs then n+1 uint32 tile starts
+  FrameArgs* h_table = nullptr;   // pinned: n FrameArgs then n uint32 tile starts
   size_t h_cap = 0;               // bytes
   void* d_table = nullptr;        // device copy of the same
   size_t d_cap = 0;
-  uint32_t* d_tile_map = nullptr;
-  size_t map_cap = 0;             // entries
   uint64_t* d_masks = nullptr;    // every mask of the tick, back to back (device)
   uint64_t* h_masks = nullptr;    // its pinned host copy
   size_t mask_cap = 0;            // bytes
@@ -115,7 +95,8 @@ struct gmm_exec {
   int device = 0;
   int M = -1, dtype = -1;
   int cu_count = 0;
-  gmm_batch_tuning tuning{256, 1024, 8};
+  gmm_batch_tuning tuning = kDefaultTuning;
+  bool shape_open = true;  // no launch shape set
   hipStream_t s_in[kCopyInStreams] = {};
   hipStream_t s_compute = nullptr, s_out = nullptr;
   std::vector<Slot> slots;
@@ -175,7 +156,6 @@ static void destroy_exec(gmm_exec* x) {
     if (s.done) (void)hipEventDestroy(s.done);
     if (s.h_table) (void)hipHostFree(s.h_table);
     if (s.d_table) (void)hipFree(s.d_table);
-    if (s.d_tile_map) (void)hipFree(s.d_tile_map);
     if (s.d_masks) (void)hipFree(s.d_masks);
     if (s.h_masks) (void)hipHostFree(s.h_masks);
   }
@@ -248,6 +228,7 @@ gmm_status gmm_exec_set_tuning(gmm_exec* x, const gmm_batch_tuning* t) {
   if (t->blocks_per_cu < 1 || t->blocks_per_cu > 32) return fail(GMM_ERR_INVALID_ARG, "blocks_per_cu must be in 1..32");
   std::lock_guard<std::mutex> lk(x->mu);
   x->tuning = *t;
+  x->shape_open = false;
   return GMM_OK;
 }
 
@@ -324,14 +305,16 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     x->cv.wait(lk, [&] { return !s.busy; });
   }
   gmm_batch_tuning tun;
+  bool open;
   {
     std::lock_guard<std::mutex> lk(x->mu);
     tun = x->tuning;
+    open = x->shape_open;
   }
   const uint32_t tile_px = static_cast<uint32_t>(tun.tile_pixels);
-  // work list: n descriptors followed by n+1 tile starts
+  // work list: n descriptors followed by n tile starts
   const size_t tab = static_cast<size_t>(n) * sizeof(FrameArgs);
-  const size_t bytes = tab + (static_cast<size_t>(n) + 1) * sizeof(uint32_t);
+  const size_t bytes = tab + static_cast<size_t>(n) * sizeof(uint32_t);
   hipError_t e = hipSuccess;
   if (bytes > s.h_cap) {
     if (s.h_table) (void)hipHostFree(s.h_table);
@@ -373,7 +356,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
   }
   s.outs.clear();
   uint32_t* h_first = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s.h_table) + tab);
-  uint64_t total_tiles = 0;
+  uint64_t total_tiles = 0, pixels = 0;
   bool measure = false;
   for (int32_t i = 0; i < n; ++i) {
     const gmm_exec_item& it = items[i];
@@ -389,17 +372,9 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     if (it.host_fused) s.outs.push_back({it.host_fused, moff[3 * i + 2], mb});
     h_first[i] = static_cast<uint32_t>(total_tiles);
     total_tiles += (static_cast<uint64_t>(h->npix) + tile_px - 1) / tile_px;
+    pixels += static_cast<uint64_t>(h->npix);
   }
   if (total_tiles >= (1ull << 31)) return fail(GMM_ERR_INVALID_ARG, "too many tiles in one tick");
-  h_first[n] = static_cast<uint32_t>(total_tiles);
-  if (total_tiles > s.map_cap) {
-    if (s.d_tile_map) (void)hipFree(s.d_tile_map);
-    s.d_tile_map = nullptr;
-    s.map_cap = 0;
-    e = hipMalloc(&s.d_tile_map, total_tiles * 2 * sizeof(uint32_t));
-    if (e != hipSuccess) return fail(GMM_ERR_OUT_OF_MEMORY, "device tile-map allocation failed");
-    s.map_cap = total_tiles * 2;
-  }
   // copy-in: frames from host memory into the streams' device frame slots, each frame on the
   // least loaded of the copy-in streams (by bytes), so several DMA engines work at once. DMA
   // engines need no compute units, so the copies of one tick overlap the previous tick's kernel.
@@ -423,21 +398,18 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     }
   }
   for (int c = 0; c < kCopyInStreams && e == hipSuccess; ++c) e = hipEventRecord(s.h2d_done[c], x->s_in[c]);
-  // compute: work list, tile map, one persistent launch over every item
+  // compute: work list, one batched launch over every item
   for (int c = 0; c < kCopyInStreams && e == hipSuccess; ++c) e = hipStreamWaitEvent(x->s_compute, s.h2d_done[c], 0);
   if (e == hipSuccess) e = hipMemcpyAsync(s.d_table, s.h_table, bytes, hipMemcpyHostToDevice, x->s_compute);
   const FrameArgs* d_tab = static_cast<const FrameArgs*>(s.d_table);
   const uint32_t* d_first = reinterpret_cast<const uint32_t*>(static_cast<const char*>(s.d_table) + tab);
   if (e == hipSuccess) {
-    tile_map_kernel<<<dim3(static_cast<unsigned>((total_tiles + kBlock - 1) / kBlock)), dim3(kBlock), 0, x->s_compute>>>(
-        d_first, static_cast<uint32_t>(n), s.d_tile_map);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {
-    const uint32_t want = static_cast<uint32_t>(tun.blocks_per_cu) * static_cast<uint32_t>(x->cu_count);
-    const dim3 grid(std::max(1u, std::min(want, static_cast<uint32_t>(total_tiles))));
-    e = launch_batch(x->M, x->dtype, tun.block_threads, grid, d_tab, s.d_tile_map, d_first,
-                     static_cast<uint32_t>(total_tiles), tile_px, measure, x->s_compute);
+    BatchLaunch l = batch_launch(tun, open, static_cast<uint32_t>(total_tiles), pixels, x->cu_count);
+    l.table = d_tab;
+    l.first = d_first;
+    l.n_streams = static_cast<uint32_t>(n);
+    l.measure = measure;
+    e = launch_batch(x->M, x->dtype, l, x->s_compute);
   }
   if (e == hipSuccess) e = hipEventRecord(s.compute_done, x->s_compute);
   // copy-out: the whole mask arena in one copy; the completion thread scatters it

@@ -1,4 +1,4 @@
-// The per-pixel body shared by every frame kernel (one stream per launch, or a persistent
+// The per-pixel body shared by every frame kernel (one stream per launch, or one
 // launch over many streams): ingest, colour and/or depth mixture step, List 1 fusion, mask
 // ballots. Keeping one body makes the plain and batched paths bit-identical by construction.
 #pragma once

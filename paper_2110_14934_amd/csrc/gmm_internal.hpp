@@ -52,10 +52,23 @@ hipError_t launch_rekey(void* st, int dtype, uint32_t tiles64, int M, int C, hip
 hipError_t launch_fill_u8(uint8_t* p, uint8_t v, int64_t n, hipStream_t s);
 
 bool frame_variant_compiled(int M, int dtype);
-// `measure`: some descriptor of the table has a traffic record (wave_bytes); otherwise the kernel
-// that never counts bytes runs.
-hipError_t launch_batch(int M, int dtype, int block, dim3 grid, const FrameArgs* table, const uint32_t* map,
-                        const uint32_t* first, uint32_t n_tiles, uint32_t tile_px, bool measure, hipStream_t s);
+// One launch of the batched kernel: the streams' descriptors and first tiles (device memory) and
+// the launch shape.
+struct BatchLaunch {
+  const FrameArgs* table;
+  const uint32_t* first;  // first tile of each stream, increasing from 0
+  uint32_t n_streams;
+  uint32_t n_pieces;      // tiles << piece_shift
+  uint32_t tile_px;       // pixels per tile
+  uint32_t piece_shift;   // a tile is 2^piece_shift pieces, one block each
+  uint32_t grid;
+  int block;              // threads per block
+  bool measure;           // some descriptor has a traffic record (wave_bytes): the kernel that counts bytes runs
+};
+constexpr gmm_batch_tuning kDefaultTuning{256, 1024, 8};
+// The launch shape for a tuning (`open`: the default, the shape left to the library).
+BatchLaunch batch_launch(const gmm_batch_tuning& t, bool open, uint32_t n_tiles, uint64_t pixels, int cu_count);
+hipError_t launch_batch(int M, int dtype, const BatchLaunch& l, hipStream_t s);
 
 inline size_t dtype_size(int dtype) { return dtype == GMM_F32 ? 4 : 2; }
 

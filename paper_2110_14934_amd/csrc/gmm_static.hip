@@ -1,14 +1,12 @@
 // Batched launch for callers that cannot allocate device memory: gmm_batch_apply_static.
 //
-// gmm_batch_apply keeps each batch's stream descriptors and tile map in device memory that
+// gmm_batch_apply keeps each batch's stream descriptors and first tiles in device memory that
 // gmm_batch_create allocates. This entry point takes the handles directly and keeps the same
 // per-call tables in one file-scope device array instead (`scratch`, below): the descriptors of
 // up to kStaticMaxStreams streams and each stream's first tile. They reach the device through
 // small pack kernels whose arguments carry kPackPerLaunch descriptors each (kernel arguments are
-// captured by value, so no host buffer has to outlive the call), and the persistent kernel finds
-// a tile's stream by a binary search over the first tiles rather than through a tile map. The
-// per-pixel body is the one every other kernel of the library runs, so results are bit-identical
-// to gmm_batch_apply.
+// captured by value, so no host buffer has to outlive the call), and the batched kernel runs on
+// them, so results are bit-identical to gmm_batch_apply.
 //
 // The array is one per device and shared by every call on that device: calls that overlap on one
 // device (different streams, or different host threads without ordering) race on it.
@@ -19,7 +17,6 @@
 #include <string>
 
 #include "gmm.h"
-#include "gmm_frame.hpp"
 #include "gmm_internal.hpp"
 
 namespace rgbd {
@@ -46,72 +43,6 @@ __global__ void __launch_bounds__(64) pack_kernel(PackArgs p, FrameArgs* __restr
   if (i < p.count) {
     table[p.base + i] = p.a[i];
     first[p.base + i] = p.first[i];
-  }
-}
-
-template <int M, typename S, int BLOCK, bool MEASURE>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5))) batch_search_kernel(const FrameArgs* __restrict__ table,
-                                                             const uint32_t* __restrict__ first,
-                                                             uint32_t n_streams, uint32_t n_tiles,
-                                                             uint32_t tile_px) {
-  __shared__ uint32_t lds[BLOCK / kWave][48];
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wv = threadIdx.x / kWave;
-  for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-    // the last stream whose first tile is <= t (first[0] = 0, increasing)
-    uint32_t lo = 0, hi = n_streams - 1;
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi + 1) >> 1;
-      if (first[mid] <= t) lo = mid;
-      else hi = mid - 1;
-    }
-    const FrameArgs a = table[lo];
-    const uint32_t t0 = (t - first[lo]) * tile_px;
-    process_tile<M, S, BLOCK, MEASURE>(a, t0, tile_px, lane, lds[wv]);
-  }
-}
-
-template <int M, typename S, bool MEASURE>
-static hipError_t launch_search_msm(int block, dim3 grid, const FrameArgs* table, const uint32_t* first,
-                                    uint32_t n, uint32_t n_tiles, uint32_t tile_px, hipStream_t s) {
-  if (block == 256)
-    batch_search_kernel<M, S, 256, MEASURE><<<grid, dim3(256), 0, s>>>(table, first, n, n_tiles, tile_px);
-  else if (block == 512)
-    batch_search_kernel<M, S, 512, MEASURE><<<grid, dim3(512), 0, s>>>(table, first, n, n_tiles, tile_px);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-template <int M, typename S>
-static hipError_t launch_search_ms(int block, dim3 grid, const FrameArgs* table, const uint32_t* first,
-                                   uint32_t n, uint32_t n_tiles, uint32_t tile_px, bool measure, hipStream_t s) {
-  return measure ? launch_search_msm<M, S, true>(block, grid, table, first, n, n_tiles, tile_px, s)
-                 : launch_search_msm<M, S, false>(block, grid, table, first, n, n_tiles, tile_px, s);
-}
-
-template <typename S>
-static hipError_t launch_search_s(int M, int block, dim3 grid, const FrameArgs* table, const uint32_t* first,
-                                  uint32_t n, uint32_t n_tiles, uint32_t tile_px, bool measure, hipStream_t s) {
-  switch (M) {
-    case 1: return launch_search_ms<1, S>(block, grid, table, first, n, n_tiles, tile_px, measure, s);
-    case 2: return launch_search_ms<2, S>(block, grid, table, first, n, n_tiles, tile_px, measure, s);
-    case 3: return launch_search_ms<3, S>(block, grid, table, first, n, n_tiles, tile_px, measure, s);
-    case 4: return launch_search_ms<4, S>(block, grid, table, first, n, n_tiles, tile_px, measure, s);
-    case 5: return launch_search_ms<5, S>(block, grid, table, first, n, n_tiles, tile_px, measure, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-// `measure`: some descriptor has a traffic record (see launch_batch).
-static hipError_t launch_search(int M, int dtype, int block, dim3 grid, const FrameArgs* table,
-                                const uint32_t* first, uint32_t n, uint32_t n_tiles, uint32_t tile_px,
-                                bool measure, hipStream_t s) {
-  switch (dtype) {
-    case GMM_F32: return launch_search_s<float>(M, block, grid, table, first, n, n_tiles, tile_px, measure, s);
-    case GMM_F16: return launch_search_s<f16s>(M, block, grid, table, first, n, n_tiles, tile_px, measure, s);
-    case GMM_BF16: return launch_search_s<bf16s>(M, block, grid, table, first, n, n_tiles, tile_px, measure, s);
-    default: return hipErrorInvalidValue;
   }
 }
 
@@ -153,7 +84,7 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
     return fail(GMM_ERR_INVALID_ARG, "n must be in 1.." + std::to_string(kStaticMaxStreams) +
                                          " (the size of the static descriptor table)");
   if (!handles || !io) return fail(GMM_ERR_INVALID_ARG, "NULL handles or io");
-  const gmm_batch_tuning t = tuning ? *tuning : gmm_batch_tuning{256, 1024, 8};
+  const gmm_batch_tuning t = tuning ? *tuning : kDefaultTuning;
   if (t.block_threads != 256 && t.block_threads != 512)
     return fail(GMM_ERR_INVALID_ARG, "block_threads must be 256 or 512");
   if (t.tile_pixels < t.block_threads || t.tile_pixels % t.block_threads || t.tile_pixels > 64 * t.block_threads)
@@ -173,7 +104,7 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
   std::sort(sorted, sorted + n);
   for (int32_t i = 1; i < n; ++i)
     if (sorted[i] == sorted[i - 1]) return fail(GMM_ERR_INVALID_ARG, "a handle appears twice");
-  uint64_t total = 0;
+  uint64_t total = 0, pixels = 0;
   for (int32_t i = 0; i < n; ++i) {
     gmm_handle* h = handles[i];
     const gmm_stream_io& s = io[i];
@@ -188,6 +119,7 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
         return fail(GMM_ERR_INVALID_ARG, "stream " + std::to_string(i) + ": fused mask not 8-byte aligned");
     }
     total += (static_cast<uint64_t>(h->npix) + t.tile_pixels - 1) / t.tile_pixels;
+    pixels += static_cast<uint64_t>(h->npix);
   }
   if (total >= (1ull << 31)) return fail(GMM_ERR_INVALID_ARG, "too many tiles in one launch");
   const int dev = handles[0]->cfg.device;
@@ -219,11 +151,12 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
     e = hipGetLastError();
   }
   if (e != hipSuccess) return hip_fail(e, "descriptor pack kernel launch");
-  const uint32_t n_tiles = static_cast<uint32_t>(total);
-  const uint32_t want = static_cast<uint32_t>(t.blocks_per_cu) * static_cast<uint32_t>(cus);
-  const dim3 grid(std::max(1u, std::min(want, n_tiles)));
-  e = launch_search(handles[0]->cfg.M, handles[0]->cfg.state_dtype, t.block_threads, grid, table, first,
-                    static_cast<uint32_t>(n), n_tiles, static_cast<uint32_t>(t.tile_pixels), measure, hs);
+  BatchLaunch l = batch_launch(t, tuning == nullptr, static_cast<uint32_t>(total), pixels, cus);
+  l.table = table;
+  l.first = first;
+  l.n_streams = static_cast<uint32_t>(n);
+  l.measure = measure;
+  e = launch_batch(handles[0]->cfg.M, handles[0]->cfg.state_dtype, l, hs);
   if (e != hipSuccess) return hip_fail(e, "static batch kernel launch");
   for (int32_t i = 0; i < n; ++i) handles[i]->last_stream = hs;
   return GMM_OK;
