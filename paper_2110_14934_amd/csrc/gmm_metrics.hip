@@ -1,9 +1,13 @@
 // Confusion counts of two bit-packed masks (the quantities of Eqs. 1-3, Sec. V.A).
 //
-// One lane per mask word: popcounts of pred&truth, pred&~truth, ~pred&~truth, ~pred&truth over
-// the valid bits, reduced across the wave with cross-lane adds, then one 64-bit atomic add per
-// wave and counter into the 4-entry result (which a first tiny kernel clears).
+// One lane per mask word: popcounts of pred & truth, pred and truth over the valid bits (TN
+// follows from the pixel count), reduced across the wave with cross-lane adds and across the block
+// through LDS. What bounds a call is launches and latency, not the masks' bytes (77 KB for a VGA
+// pair), so masks up to kOneBlockWords are counted by one block that writes the four counts
+// itself; larger ones by many blocks that add to counts which a first tiny kernel clears.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "gmm.h"
 #include "gmm_internal.hpp"
@@ -14,39 +18,88 @@ __global__ void __launch_bounds__(4) clear_counts_kernel(unsigned long long* cou
   if (threadIdx.x < 4) counts[threadIdx.x] = 0ull;
 }
 
-__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
+// Set bits of (pred & truth, pred, truth): 32 bits hold a wave's (512 blocks of 16 waves reach them
+// past 2^39 words).
+struct Ones {
+  uint32_t both, pred, truth;
+};
+
+__device__ __forceinline__ Ones wave_sum(Ones v) {
 #pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
+  for (int d = kWave / 2; d > 0; d >>= 1) {
+    v.both += __shfl_xor(v.both, d, kWave);
+    v.pred += __shfl_xor(v.pred, d, kWave);
+    v.truth += __shfl_xor(v.truth, d, kWave);
+  }
   return v;
 }
 
-__global__ void __launch_bounds__(kBlock) confusion_kernel(const uint64_t* __restrict__ pred,
-                                                           const uint64_t* __restrict__ truth,
-                                                           int64_t npix, int64_t nwords,
-                                                           unsigned long long* counts) {
-  unsigned long long tp = 0, fp = 0, tn = 0, fn = 0;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t w = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; w < nwords; w += stride) {
-    const uint64_t p = pred[w];
-    const uint64_t t = truth[w];
-    const int64_t rem = npix - w * 64;
-    const uint64_t valid = rem >= 64 ? ~0ull : ((1ull << rem) - 1ull);
-    tp += __popcll(p & t & valid);
-    fp += __popcll(p & ~t & valid);
-    tn += __popcll(~p & ~t & valid);
-    fn += __popcll(~p & t & valid);
+// Words first, first + step, ... of the masks, eight in flight.
+__device__ __forceinline__ Ones count_words(const uint64_t* __restrict__ pred, const uint64_t* __restrict__ truth,
+                                            uint64_t first, uint64_t step, uint64_t nwords, uint64_t last_valid) {
+  Ones o{0, 0, 0};
+  constexpr uint32_t U = 4;
+  for (uint64_t w = first; w < nwords; w += U * step) {
+    uint64_t p[U], t[U];
+#pragma unroll
+    for (uint32_t j = 0; j < U; ++j) {
+      const uint64_t at = w + j * step;
+      p[j] = at < nwords ? pred[at] : 0ull;
+      t[j] = at < nwords ? truth[at] : 0ull;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < U; ++j) {
+      const uint64_t valid = w + j * step == nwords - 1 ? last_valid : ~0ull;
+      o.both += __popcll(p[j] & t[j] & valid);
+      o.pred += __popcll(p[j] & valid);
+      o.truth += __popcll(t[j] & valid);
+    }
   }
-  tp = wave_sum(tp);
-  fp = wave_sum(fp);
-  tn = wave_sum(tn);
-  fn = wave_sum(fn);
-  if ((threadIdx.x & (kWave - 1)) == 0) {
-    atomicAdd(&counts[0], tp);
-    atomicAdd(&counts[1], fp);
-    atomicAdd(&counts[2], tn);
-    atomicAdd(&counts[3], fn);
+  return o;
+}
+
+constexpr int kCountBlock = 1024;
+
+template <bool ALONE>
+__global__ void __launch_bounds__(kCountBlock) confusion_kernel(const uint64_t* __restrict__ pred,
+                                                          const uint64_t* __restrict__ truth, uint64_t npix,
+                                                          uint64_t nwords, unsigned long long* __restrict__ counts) {
+  constexpr int WAVES = kCountBlock / kWave;
+  __shared__ Ones part[WAVES];
+  const uint32_t rem = static_cast<uint32_t>(npix & 63u);
+  const uint64_t last_valid = rem ? (1ull << rem) - 1ull : ~0ull;
+  const Ones o = wave_sum(count_words(pred, truth, blockIdx.x * kCountBlock + threadIdx.x, gridDim.x * kCountBlock,
+                                           nwords, last_valid));
+  if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = o;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  uint64_t both = 0, p = 0, t = 0;
+  for (int i = 0; i < WAVES; ++i) {
+    both += part[i].both;
+    p += part[i].pred;
+    t += part[i].truth;
+  }
+  if constexpr (ALONE) {
+    counts[0] = both;
+    counts[1] = p - both;
+    counts[2] = npix + both - p - t;
+    counts[3] = t - both;
+  } else {  // the pixel count enters once; the sum is exact modulo 2^64
+    atomicAdd(&counts[0], both);
+    atomicAdd(&counts[1], p - both);
+    atomicAdd(&counts[2], (blockIdx.x == 0 ? npix : 0ull) + both - p - t);
+    atomicAdd(&counts[3], t - both);
   }
 }
+
+// One block, one launch up to kOneBlockWords: a VGA mask 3.4 us on the GPU and 6.7 us a call from
+// Python, where clearing and counting in many blocks takes 5.6 and 9.5 us; 10^6 pixels 5.8 and 6.7
+// against 5.6 and 9.5; a 1920x1080 mask 9.7 against 5.0 on the GPU. Above it, blocks of
+// kWordsPerBlock words: the adds of all blocks meet at one cache line, and 64 of them cost less
+// than 1024 (3840x2160: 5.9 us, with a block per 256 words 28 us, and with an add for every wave
+// besides 101 us).
+constexpr uint64_t kOneBlockWords = 16384;
+constexpr uint64_t kWordsPerBlock = 4096;
 
 }  // namespace rgbd
 
@@ -60,14 +113,21 @@ extern "C" gmm_status gmm_mask_confusion(const uint64_t* pred, const uint64_t* t
        reinterpret_cast<uintptr_t>(counts)) % 8)
     return fail(GMM_ERR_INVALID_ARG, "masks and counts must be 8-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int64_t nwords = (npix + 63) / 64;
-  const int64_t blocks = std::min<int64_t>((nwords + kBlock - 1) / kBlock, 1024);
+  const uint64_t n = static_cast<uint64_t>(npix);
+  const uint64_t words = (n + 63) / 64;
   auto* c = reinterpret_cast<unsigned long long*>(counts);
-  clear_counts_kernel<<<1, 4, 0, s>>>(c);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) {
-    confusion_kernel<<<dim3(static_cast<unsigned>(blocks)), dim3(kBlock), 0, s>>>(pred, truth, npix, nwords, c);
+  hipError_t e = hipSuccess;
+  if (words <= kOneBlockWords) {
+    confusion_kernel<true><<<1, dim3(kCountBlock), 0, s>>>(pred, truth, n, words, c);
     e = hipGetLastError();
+  } else {
+    const uint64_t blocks = std::min<uint64_t>((words + kWordsPerBlock - 1) / kWordsPerBlock, 512u);
+    clear_counts_kernel<<<1, 4, 0, s>>>(c);
+    e = hipGetLastError();
+    if (e == hipSuccess) {
+      confusion_kernel<false><<<dim3(static_cast<unsigned>(blocks)), dim3(kCountBlock), 0, s>>>(pred, truth, n, words, c);
+      e = hipGetLastError();
+    }
   }
   if (e != hipSuccess) return hip_fail(e, "confusion kernel launch");
   return GMM_OK;
