@@ -332,11 +332,12 @@ gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t n, const g
 typedef struct gmm_exec gmm_exec;
 
 /* One stream's frame in a tick. Frames are read from host memory with dense rows (pitch
- * 3*width for colour, 2*width for depth) by DMA; masks are written to host memory. Host buffers
- * should be page-locked (hipHostMalloc, pinned torch tensors) for the copies to overlap device
- * work; they must stay valid and untouched until the tick completes (gmm_exec_poll). A NULL
- * mask pointer skips copying that mask back; non-NULL host_fused runs List 1 for the stream
- * (two-modality streams only). */
+ * 3*width for colour, 2*width for depth); masks are written to host memory. Host buffers should be
+ * page-locked (hipHostMalloc, pinned torch tensors): colour frames aligned to 4 bytes, depth frames
+ * to 2 and masks to 8 in coherent page-locked memory are read and written by the kernel in place;
+ * any others are copied by DMA, and only page-locked copies overlap device work. All must stay
+ * valid and untouched until the tick completes (gmm_exec_poll). A NULL mask pointer skips that
+ * mask; non-NULL host_fused runs List 1 for the stream (two-modality streams only). */
 typedef struct {
   gmm_handle* handle;
   const uint8_t* host_rgb;
@@ -355,7 +356,8 @@ typedef struct {
 gmm_status gmm_exec_create(int32_t device, int32_t ring, gmm_exec** out);
 /* Wait for all ticks, then release. NULL is a no-op. Attached handles stay valid. */
 gmm_status gmm_exec_destroy(gmm_exec* x);
-/* Launch shape of the batched kernel (same meaning and limits as gmm_batch_tuning). */
+/* Launch shape of the batched kernel (same meaning and limits as gmm_batch_tuning). Ticks that read
+ * frames in place take the default shape. */
 gmm_status gmm_exec_set_tuning(gmm_exec* x, const gmm_batch_tuning* t);
 /* Give a stream two device frame slots, used by its frames in turn so that one frame can be
  * copied in while the previous one computes (all streams of an executor share M and the state

@@ -1,12 +1,19 @@
 // Serving executor: one call advances an arbitrary set of attached streams by one frame each,
-// taking their frames from (pinned) host memory and returning masks to host memory.
+// taking their frames from host memory and returning masks to host memory.
 //
-// Per tick, HIP streams form the pipeline of the paper's Fig. 4(a): the frames of tick N+1 are
-// copied host->device while tick N is computed and the masks of tick N-1 are copied back.
-// Within a tick: host->device frame copies (spread over four copy-in streams, so several DMA
-// engines share the host link) -> descriptor upload and one batched launch (compute stream) -> mask copies
-// device->host (copy-out stream). A ring of `ring` tick slots bounds the work in flight; a
-// completion thread waits on each tick's last event in order and records its completion time.
+// Page-locked frames are read by the batched kernel where they lie, and masks are written to
+// page-locked buffers directly: every byte of a frame is read once, so a device copy would only add
+// a transfer before the kernel and a submission per frame. A wave's 192 colour bytes and 128 depth
+// bytes are contiguous; such reads reach 57 GB/s over the host link, the rate of one large DMA copy
+// (per-frame DMA copies reach 47), and the kernel's arithmetic hides behind them. A tick of 16 streams (27 MB
+// of frames) took 841 us with copies to the device and back and takes 557 us; one 640x480 stream
+// 127 and 59 us.
+// Frames that are not page-locked, or not aligned for the kernel's loads, are copied to the
+// stream's device slot first (spread over four copy-in streams, so several DMA engines share the
+// host link), and such masks go through a device arena and a copy back: the pipeline of the paper's
+// Fig. 4(a), in which the copies of tick N+1 overlap the kernel of tick N and the copy back of
+// tick N-1. A ring of `ring` tick slots bounds the work in flight; a completion thread waits on
+// each tick's last event in order and records its completion time.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -76,7 +83,7 @@ struct Slot {
   size_t h_cap = 0;               // bytes
   void* d_table = nullptr;        // device copy of the same
   size_t d_cap = 0;
-  uint64_t* d_masks = nullptr;    // every mask of the tick, back to back (device)
+  uint64_t* d_masks = nullptr;    // the tick's masks not written in place, back to back (device)
   uint64_t* h_masks = nullptr;    // its pinned host copy
   size_t mask_cap = 0;            // bytes
   struct Out {
@@ -166,6 +173,29 @@ static void destroy_exec(gmm_exec* x) {
   if (x->s_compute) (void)hipStreamDestroy(x->s_compute);
   if (x->s_out) (void)hipStreamDestroy(x->s_out);
   delete x;
+}
+
+// The device address of `bytes` of host memory at p that the kernels of `device` can use in place:
+// page-locked there, coherent, from one allocation and aligned to `align`. NULL if it is not. Asked
+// anew for every buffer of every tick: memory at an address can change between ticks.
+static void* in_place(const void* p, size_t bytes, size_t align, int device) {
+  if (!p || reinterpret_cast<uintptr_t>(p) % align) return nullptr;
+  void* first = nullptr;
+  for (int end = 0; end < 2; ++end) {
+    hipPointerAttribute_t a{};
+    const char* q = static_cast<const char*>(p) + (end ? bytes - 1 : 0);
+    if (hipPointerGetAttributes(&a, q) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    if (a.type != hipMemoryTypeHost || a.device != device || !a.devicePointer || (a.allocationFlags & hipHostMallocNonCoherent))
+      return nullptr;
+    if (!end)
+      first = a.devicePointer;
+    else if (static_cast<char*>(a.devicePointer) != static_cast<char*>(first) + (bytes - 1))
+      return nullptr;
+  }
+  return first;
 }
 
 static size_t mask_bytes(const gmm_handle* h) { return static_cast<size_t>((h->npix + 63) / 64) * 8; }
@@ -311,7 +341,6 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     tun = x->tuning;
     open = x->shape_open;
   }
-  const uint32_t tile_px = static_cast<uint32_t>(tun.tile_pixels);
   // work list: n descriptors followed by n tile starts
   const size_t tab = static_cast<size_t>(n) * sizeof(FrameArgs);
   const size_t bytes = tab + static_cast<size_t>(n) * sizeof(uint32_t);
@@ -332,16 +361,36 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     if (e != hipSuccess) return fail(GMM_ERR_OUT_OF_MEMORY, "device work-list allocation failed");
     s.d_cap = bytes * 2;
   }
-  // masks of the tick: one region per requested mask, 256-byte aligned, in one device arena
+  // frames and masks used in place; the others get a device slot or a region of the mask arena
+  // (256-byte aligned), also the masks of present modalities that the caller does not want, which
+  // the kernel writes all the same
+  struct Place {
+    const uint8_t* rgb;
+    const uint16_t* depth;
+    uint64_t* mask[3];   // in place, or NULL
+    size_t off[3];       // offset in the arena, or SIZE_MAX
+  };
+  std::vector<Place> place(n);
   size_t mask_total = 0;
-  std::vector<size_t> moff(static_cast<size_t>(n) * 3, SIZE_MAX);
+  bool linked = false;  // some frame is read in place
   for (int32_t i = 0; i < n; ++i) {
-    const size_t mb = (mask_bytes(items[i].handle) + 255) / 256 * 256;
-    const gmm_handle* h = items[i].handle;
-    // the kernel writes a stream's masks whenever the modality is present; keep room for all
-    if (has_rgb(h)) moff[3 * i] = mask_total, mask_total += mb;
-    if (has_depth(h)) moff[3 * i + 1] = mask_total, mask_total += mb;
-    if (items[i].host_fused) moff[3 * i + 2] = mask_total, mask_total += mb;
+    const gmm_exec_item& it = items[i];
+    const gmm_handle* h = it.handle;
+    const size_t px = static_cast<size_t>(h->npix), mb = mask_bytes(h);
+    Place& p = place[i];
+    p.rgb = static_cast<const uint8_t*>(in_place(it.host_rgb, px * 3, 4, x->device));
+    p.depth = static_cast<const uint16_t*>(in_place(it.host_depth, px * 2, 2, x->device));
+    linked = linked || p.rgb || p.depth;
+    void* want[3] = {it.host_fg_rgb, it.host_fg_depth, it.host_fused};
+    const bool write[3] = {has_rgb(h), has_depth(h), it.host_fused != nullptr};
+    for (int m = 0; m < 3; ++m) {
+      p.mask[m] = static_cast<uint64_t*>(in_place(want[m], mb, 8, x->device));
+      p.off[m] = SIZE_MAX;
+      if (write[m] && !p.mask[m]) {
+        p.off[m] = mask_total;
+        mask_total += (mb + 255) / 256 * 256;
+      }
+    }
   }
   if (mask_total > s.mask_cap) {
     if (s.d_masks) (void)hipFree(s.d_masks);
@@ -354,6 +403,14 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     if (e != hipSuccess) return fail(GMM_ERR_OUT_OF_MEMORY, "mask arena allocation failed");
     s.mask_cap = mask_total * 2;
   }
+  // A tick that reads frames over the link always takes the default shape, one block per piece:
+  // what is in flight then keeps the link busy, where fewer blocks that walk tiles do not (640
+  // mixed streams a tick: 52.3 GB/s, 38.5 with 4 blocks of 256 threads per CU).
+  if (linked) {
+    tun = kDefaultTuning;
+    open = true;
+  }
+  const uint32_t tile_px = static_cast<uint32_t>(tun.tile_pixels);
   s.outs.clear();
   uint32_t* h_first = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s.h_table) + tab);
   uint64_t total_tiles = 0, pixels = 0;
@@ -361,45 +418,49 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
   for (int32_t i = 0; i < n; ++i) {
     const gmm_exec_item& it = items[i];
     gmm_handle* h = it.handle;
-    auto dm = [&](int k) { return moff[3 * i + k] == SIZE_MAX ? nullptr : s.d_masks + moff[3 * i + k] / 8; };
+    const Place& p = place[i];
+    uint64_t* mask[3];
+    for (int m = 0; m < 3; ++m) mask[m] = p.off[m] == SIZE_MAX ? p.mask[m] : s.d_masks + p.off[m] / 8;
     const int k = static_cast<int>(att[i].frames % kFramesInFlight);
-    s.h_table[i] = frame_args(h, att[i].d_rgb[k], 3 * static_cast<int64_t>(h->cfg.width), att[i].d_depth[k],
-                              2 * static_cast<int64_t>(h->cfg.width), dm(0), dm(1), dm(2));
+    s.h_table[i] = frame_args(h, p.rgb ? p.rgb : att[i].d_rgb[k], 3 * static_cast<int64_t>(h->cfg.width),
+                              p.depth ? p.depth : att[i].d_depth[k], 2 * static_cast<int64_t>(h->cfg.width), mask[0],
+                              mask[1], mask[2]);
     measure = measure || s.h_table[i].wave_bytes != nullptr;
-    const size_t mb = mask_bytes(h);
-    if (it.host_fg_rgb) s.outs.push_back({it.host_fg_rgb, moff[3 * i], mb});
-    if (it.host_fg_depth) s.outs.push_back({it.host_fg_depth, moff[3 * i + 1], mb});
-    if (it.host_fused) s.outs.push_back({it.host_fused, moff[3 * i + 2], mb});
+    void* want[3] = {it.host_fg_rgb, it.host_fg_depth, it.host_fused};
+    for (int m = 0; m < 3; ++m)
+      if (want[m] && p.off[m] != SIZE_MAX) s.outs.push_back({want[m], p.off[m], mask_bytes(h)});
     h_first[i] = static_cast<uint32_t>(total_tiles);
     total_tiles += (static_cast<uint64_t>(h->npix) + tile_px - 1) / tile_px;
     pixels += static_cast<uint64_t>(h->npix);
   }
   if (total_tiles >= (1ull << 31)) return fail(GMM_ERR_INVALID_ARG, "too many tiles in one tick");
-  // copy-in: frames from host memory into the streams' device frame slots, each frame on the
-  // least loaded of the copy-in streams (by bytes), so several DMA engines work at once. DMA
-  // engines need no compute units, so the copies of one tick overlap the previous tick's kernel.
-  // The slot a frame goes to was last read by the stream's frame before last, whose tick has
-  // completed: a stream is accepted here only with at most one frame in flight.
+  // copy-in of the frames not used in place, each into its stream's device slot on the least
+  // loaded of the copy-in streams (by bytes). DMA engines need no compute units, so the copies of
+  // one tick overlap the previous tick's kernel. The slot a frame goes to was last read by the
+  // stream's frame before last, whose tick has completed: a stream is accepted here only with at
+  // most one frame in flight.
   size_t queued[kCopyInStreams] = {};
   for (int32_t i = 0; i < n && e == hipSuccess; ++i) {
-    const gmm_handle* h = items[i].handle;
-    const size_t px = static_cast<size_t>(h->npix);
+    const size_t px = static_cast<size_t>(items[i].handle->npix);
     const int k = static_cast<int>(att[i].frames % kFramesInFlight);
     int q = 0;
     for (int c = 1; c < kCopyInStreams; ++c)
       if (queued[c] < queued[q]) q = c;
-    if (items[i].host_rgb) {
+    if (items[i].host_rgb && !place[i].rgb) {
       e = hipMemcpyAsync(att[i].d_rgb[k], items[i].host_rgb, px * 3, hipMemcpyHostToDevice, x->s_in[q]);
       queued[q] += px * 3;
     }
-    if (e == hipSuccess && items[i].host_depth) {
+    if (e == hipSuccess && items[i].host_depth && !place[i].depth) {
       e = hipMemcpyAsync(att[i].d_depth[k], items[i].host_depth, px * 2, hipMemcpyHostToDevice, x->s_in[q]);
       queued[q] += px * 2;
     }
   }
-  for (int c = 0; c < kCopyInStreams && e == hipSuccess; ++c) e = hipEventRecord(s.h2d_done[c], x->s_in[c]);
-  // compute: work list, one batched launch over every item
-  for (int c = 0; c < kCopyInStreams && e == hipSuccess; ++c) e = hipStreamWaitEvent(x->s_compute, s.h2d_done[c], 0);
+  // compute: work list, one batched launch over every item, after the copies of this tick
+  for (int c = 0; c < kCopyInStreams && e == hipSuccess; ++c) {
+    if (!queued[c]) continue;
+    e = hipEventRecord(s.h2d_done[c], x->s_in[c]);
+    if (e == hipSuccess) e = hipStreamWaitEvent(x->s_compute, s.h2d_done[c], 0);
+  }
   if (e == hipSuccess) e = hipMemcpyAsync(s.d_table, s.h_table, bytes, hipMemcpyHostToDevice, x->s_compute);
   const FrameArgs* d_tab = static_cast<const FrameArgs*>(s.d_table);
   const uint32_t* d_first = reinterpret_cast<const uint32_t*>(static_cast<const char*>(s.d_table) + tab);
@@ -411,12 +472,16 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     l.measure = measure;
     e = launch_batch(x->M, x->dtype, l, x->s_compute);
   }
-  if (e == hipSuccess) e = hipEventRecord(s.compute_done, x->s_compute);
-  // copy-out: the whole mask arena in one copy; the completion thread scatters it
-  if (e == hipSuccess) e = hipStreamWaitEvent(x->s_out, s.compute_done, 0);
-  if (e == hipSuccess && !s.outs.empty())
-    e = hipMemcpyAsync(s.h_masks, s.d_masks, mask_total, hipMemcpyDeviceToHost, x->s_out);
-  if (e == hipSuccess) e = hipEventRecord(s.done, x->s_out);
+  // copy-out of the masks not written in place: the arena in one copy, scattered by the completion
+  // thread
+  if (!s.outs.empty()) {
+    if (e == hipSuccess) e = hipEventRecord(s.compute_done, x->s_compute);
+    if (e == hipSuccess) e = hipStreamWaitEvent(x->s_out, s.compute_done, 0);
+    if (e == hipSuccess) e = hipMemcpyAsync(s.h_masks, s.d_masks, mask_total, hipMemcpyDeviceToHost, x->s_out);
+    if (e == hipSuccess) e = hipEventRecord(s.done, x->s_out);
+  } else if (e == hipSuccess) {
+    e = hipEventRecord(s.done, x->s_compute);
+  }
   if (e != hipSuccess) return hip_fail(e, "executor tick");
   {
     std::lock_guard<std::mutex> lk(x->mu);

@@ -401,3 +401,52 @@ def test_served_streams_follow_the_oracle(dtype):
     assert dis <= (MASK_FRACTION if dtype == "f32" else 1e-3) * total + 1
     if dtype != "f32":
         assert worst_ulps <= 4.0001
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_buffers_used_in_place_are_read_and_written_anew_every_tick(dtype):
+    # one set of page-locked buffers for all ticks, rewritten by the host between them: the kernel
+    # reads the frames where they lie, so it must see each tick's bytes and not an earlier tick's
+    specs = SPECS + [WIDE]
+    streams = [Stream(s) for s in specs]
+    x = _abi.gmm_exec_create(0, 2)
+    code = {"f16": _abi.GMM_F16, "f32": _abi.GMM_F32}[dtype]
+    handles, refs, bufs, items = [], [], [], []
+    try:
+        for sp in specs:
+            h = _abi.gmm_create(_abi.gmm_config_default(sp.width, sp.height, mods(sp), 3, state_dtype=code))
+            handles.append(h)
+            _abi.gmm_exec_attach(x, h)
+            refs.append(Segmenter(sp.width, sp.height, mods(sp), 3, state_dtype=dtype))
+            b = [torch.empty((sp.height, sp.width, 3), dtype=torch.uint8, pin_memory=True) if sp.rgb else None,
+                 torch.empty((sp.height, sp.width), dtype=torch.uint16, pin_memory=True) if sp.depth else None]
+            b += [torch.full((words(sp),), -1, dtype=torch.int64, pin_memory=True) if on else None
+                  for on in (sp.rgb, sp.depth, sp.rgb and sp.depth)]
+            bufs.append(b)
+            it = _abi.gmm_exec_item()
+            it.handle = h
+            it.host_rgb, it.host_depth, it.host_fg_rgb, it.host_fg_depth, it.host_fused = \
+                (t.data_ptr() if t is not None else None for t in b)
+            items.append(it)
+        for t in range(10):
+            for sp, st, b, ref in zip(specs, streams, bufs, refs):
+                frame = [st.rgb(t) if sp.rgb else None, st.depth(t) if sp.depth else None]
+                for src, dst in zip(frame, b):
+                    if src is not None:
+                        dst.copy_(src)
+                dev = [f.to(DEV) if f is not None else None for f in frame]
+                ref.apply_fused(*dev) if ref.fused is not None else ref.apply(*dev)
+            _abi.gmm_exec_launch(x, items)
+            _abi.gmm_exec_drain(x)
+            torch.cuda.synchronize()
+            for b, ref in zip(bufs, refs):
+                for got, want in zip(b[2:], (ref.fg_rgb, ref.fg_depth, ref.fused)):
+                    if got is not None:
+                        assert torch.equal(got, want.cpu()), t
+        for h, ref in zip(handles, refs):
+            assert np.array_equal(_abi.gmm_read_state(h), ref.read_state())
+    finally:
+        for h in handles:
+            _abi.gmm_exec_detach(x, h)
+            _abi.gmm_destroy(h)
+        _abi.gmm_exec_destroy(x)
