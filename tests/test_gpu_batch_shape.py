@@ -12,8 +12,9 @@ pytestmark = pytest.mark.gpu
 MODS = (GMM_RGB | GMM_DEPTH, GMM_RGB, GMM_DEPTH)
 
 
-def _streams(sizes, dtype):
-    return [Segmenter(w, h, MODS[i % 3], 2, state_dtype=dtype) for i, (w, h) in enumerate(sizes)]
+def _streams(sizes, dtype, alphas):
+    return [Segmenter(w, h, MODS[i % 3], 2, state_dtype=dtype, alpha=alphas[i % len(alphas)])
+            for i, (w, h) in enumerate(sizes)]
 
 
 def _frames(sizes, gen):
@@ -26,10 +27,10 @@ def _frames(sizes, gen):
     return out
 
 
-def _check(sizes, call, dtype, sets=3):
+def _check(sizes, call, dtype, sets=3, alphas=(0.05,)):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(len(sizes))
-    one, many = _streams(sizes, dtype), _streams(sizes, dtype)
+    one, many = _streams(sizes, dtype, alphas), _streams(sizes, dtype, alphas)
     batch = Batch(many) if call == "apply" else None
     for _ in range(sets):
         frames = _frames(sizes, gen)
@@ -62,3 +63,10 @@ def test_every_piece_finds_its_stream(n, call):
 def test_default_pieces_cover_every_pixel(extra, dtype):
     sizes = [(w, 1) for w in (1, 63, 255, 256, 257, 511, 512, 513, 767, 769, 1023, 1024, 1025, 2049)]
     _check(sizes + extra, "apply", dtype)
+
+
+# the static call sends the model constants once per group of equal ones: none alike, and groups
+# that end inside and at the end of a launch's 32 streams
+@pytest.mark.parametrize("n,alphas", [(40, (0.05, 0.02)), (70, (0.05,) * 32 + (0.02,) * 5), (33, (0.05,) * 32 + (0.1,))])
+def test_static_streams_keep_their_own_constants(n, alphas):
+    _check([(65 + i, 3) for i in range(n)], "static", "f16", alphas=alphas)
