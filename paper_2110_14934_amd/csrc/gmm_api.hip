@@ -174,6 +174,13 @@ hipError_t rgbd::init_state(gmm_handle* h, hipStream_t s) {
   return e;
 }
 
+size_t rgbd::hot_bytes(const gmm_handle* h) {
+  const uint32_t M = static_cast<uint32_t>(h->cfg.M), es = static_cast<uint32_t>(h->esize);
+  const size_t rgb = !has_rgb(h) ? 0 : tile_layout(M, is_augmented(h) ? 4 : 3, es).hot + 3;
+  const size_t depth = !has_depth(h) ? 0 : (sep_depth(h) ? tile_layout(M, 1, es).hot + 1 : 0) + 2;
+  return static_cast<size_t>(h->npix) * (rgb + depth);
+}
+
 size_t rgbd::state_bytes(const gmm_handle* h) { return h->rgb_bytes + h->depth_bytes + h->fuse_bytes; }
 
 extern "C" {
@@ -337,7 +344,7 @@ gmm_status gmm_apply_frame(gmm_handle* h, const uint8_t* rgb, int64_t rgb_pitch_
   const FrameArgs a = frame_args(h, rgb, rgb_pitch_bytes, depth, depth_pitch_bytes, fg_rgb, fg_depth, nullptr);
   const int mode = (has_rgb(h) ? kModeRGB : 0) | (has_depth(h) ? kModeDepth : 0);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, mode, streams_state(h), s);
+  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, mode, streams_rows(hot_bytes(h)), s);
   if (e != hipSuccess) return hip_fail(e, "frame kernel launch");
   h->last_stream = s;
   return GMM_OK;
@@ -374,7 +381,7 @@ gmm_status gmm_apply_frame_fused(gmm_handle* h, const uint8_t* rgb, int64_t rgb_
   if (!g.ok()) return fail(GMM_ERR_DEVICE, "cannot select the handle's device");
   const FrameArgs a = frame_args(h, rgb, rgb_pitch_bytes, depth, depth_pitch_bytes, fg_rgb, fg_depth, fused);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, kModeRGB | kModeDepth | kModeFuse, streams_state(h), s);
+  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, kModeRGB | kModeDepth | kModeFuse, streams_rows(hot_bytes(h)), s);
   if (e != hipSuccess) return hip_fail(e, "fused frame kernel launch");
   h->last_stream = s;
   return GMM_OK;
@@ -396,7 +403,7 @@ gmm_status gmm_apply_frame_augmented(gmm_handle* h, const uint8_t* rgb, int64_t 
   if (!g.ok()) return fail(GMM_ERR_DEVICE, "cannot select the handle's device");
   const FrameArgs a = frame_args(h, rgb, rgb_pitch_bytes, depth, depth_pitch_bytes, fg, nullptr, nullptr);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, kModeAug, streams_state(h), s);
+  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, kModeAug, streams_rows(hot_bytes(h)), s);
   if (e != hipSuccess) return hip_fail(e, "augmented frame kernel launch");
   h->last_stream = s;
   return GMM_OK;

@@ -46,9 +46,11 @@ __device__ __forceinline__ uint32_t find_stream(const uint32_t* __restrict__ fir
 // Five waves per SIMD: the body fits them without spilling (checked at build time by the tests).
 // A block takes one piece of a tile (tile_px >> piece_shift pixels) and the grid usually has a
 // block for every piece (batch_launch below); a smaller grid walks the pieces b, b+G, b+2G, ...
+// CP: the cache policy of the rows (kCached or kStream; streams_rows).
 // MEASURE: the body that adds each wave's state bytes to the streams' traffic records; the launch
-// takes it only when a stream of the batch has one, so the common body never forms the counts.
-template <int M, typename S, int BLOCK, bool MEASURE>
+// takes it (with kStream) only when a stream of the batch has one, so the common body never forms
+// the counts.
+template <int M, typename S, int BLOCK, int CP, bool MEASURE>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5))) batch_kernel(const FrameArgs* __restrict__ table,
                                                       const uint32_t* __restrict__ first, uint32_t n_streams,
                                                       uint32_t n_pieces, uint32_t tile_px, uint32_t piece_shift) {
@@ -61,17 +63,17 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5)))
     const uint32_t s = find_stream(first, n_streams, t);
     const FrameArgs a = table[s];
     const uint32_t t0 = (t - first[s]) * tile_px + (b & part_mask) * piece_px;
-    process_tile<M, S, BLOCK, MEASURE>(a, t0, piece_px, lane, lds[wv]);
+    process_tile<M, S, BLOCK, CP, MEASURE>(a, t0, piece_px, lane, lds[wv]);
   }
 }
 
-template <int M, typename S, bool MEASURE>
-static hipError_t launch_batch_msm(const BatchLaunch& l, hipStream_t s) {
+template <int M, typename S, int CP, bool MEASURE>
+static hipError_t launch_batch_mscm(const BatchLaunch& l, hipStream_t s) {
   const dim3 grid(l.grid);
   if (l.block == 256)
-    batch_kernel<M, S, 256, MEASURE><<<grid, dim3(256), 0, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
+    batch_kernel<M, S, 256, CP, MEASURE><<<grid, dim3(256), 0, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
   else if (l.block == 512)
-    batch_kernel<M, S, 512, MEASURE><<<grid, dim3(512), 0, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
+    batch_kernel<M, S, 512, CP, MEASURE><<<grid, dim3(512), 0, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -79,7 +81,8 @@ static hipError_t launch_batch_msm(const BatchLaunch& l, hipStream_t s) {
 
 template <int M, typename S>
 static hipError_t launch_batch_ms(const BatchLaunch& l, hipStream_t s) {
-  return l.measure ? launch_batch_msm<M, S, true>(l, s) : launch_batch_msm<M, S, false>(l, s);
+  if (l.measure) return launch_batch_mscm<M, S, kStream, true>(l, s);
+  return l.stream ? launch_batch_mscm<M, S, kStream, false>(l, s) : launch_batch_mscm<M, S, kCached, false>(l, s);
 }
 
 template <typename S>
@@ -152,6 +155,7 @@ struct gmm_batch {
   uint32_t* d_first_tile = nullptr;
   uint32_t n_tiles = 0;
   uint64_t pixels = 0;                       // of one frame of every stream
+  size_t hot = 0;                            // hot_bytes of all streams
   gmm_batch_tuning tuning = kDefaultTuning;
   bool shape_open = true;                    // no launch shape set or found: batch_launch may cut the tiles
   hipStream_t last_stream = nullptr;
@@ -175,10 +179,12 @@ static gmm_status build_tiles(gmm_batch* b, uint32_t tile_px) {
   std::vector<uint32_t> first(n_streams(b));
   uint64_t total = 0;
   b->pixels = 0;
+  b->hot = 0;
   for (size_t i = 0; i < n_streams(b); ++i) {
     first[i] = static_cast<uint32_t>(total);
     total += (static_cast<uint64_t>(b->handles[i]->npix) + tile_px - 1) / tile_px;
     b->pixels += static_cast<uint64_t>(b->handles[i]->npix);
+    b->hot += hot_bytes(b->handles[i]);
   }
   if (total >= (1ull << 31)) return fail(GMM_ERR_INVALID_ARG, "too many tiles in one batch");
   const hipError_t e = hipMemcpy(b->d_first_tile, first.data(), first.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
@@ -203,6 +209,7 @@ static hipError_t run_slot(gmm_batch* b, int slot, hipStream_t s) {
   l.first = b->d_first_tile;
   l.n_streams = static_cast<uint32_t>(n_streams(b));
   l.measure = b->slot_measure[slot] != 0;
+  l.stream = streams_rows(b->hot);
   return launch_batch(b->M, b->dtype, l, s);
 }
 

@@ -108,6 +108,7 @@ struct gmm_exec {
   hipStream_t s_compute = nullptr, s_out = nullptr;
   std::vector<Slot> slots;
   std::map<const gmm_handle*, Attached> attached;
+  size_t hot = 0;  // hot_bytes of the attached streams: what competes for the last-level cache between a stream's frames
   uint64_t next_tick = 1;
   // completion thread
   std::mutex mu;
@@ -280,6 +281,7 @@ gmm_status gmm_exec_attach(gmm_exec* x, gmm_handle* h, size_t* device_bytes) {
   place_slots(a, h, static_cast<uint8_t*>(mem));
   a.bytes = slots;
   x->attached[h] = a;
+  x->hot += hot_bytes(h);
   x->M = h->cfg.M;
   x->dtype = h->cfg.state_dtype;
   if (device_bytes) *device_bytes = a.bytes;
@@ -294,6 +296,7 @@ gmm_status gmm_exec_detach(gmm_exec* x, gmm_handle* h) {
   x->cv.wait(lk, [&] { return it->second.in_flight == 0; });  // its last frame has completed
   void* base = it->second.base;
   x->attached.erase(it);
+  x->hot -= hot_bytes(h);
   lk.unlock();
   DeviceGuard g(x->device);
   if (base) (void)hipFree(base);
@@ -336,10 +339,12 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
   }
   gmm_batch_tuning tun;
   bool open;
+  size_t hot;
   {
     std::lock_guard<std::mutex> lk(x->mu);
     tun = x->tuning;
     open = x->shape_open;
+    hot = x->hot;
   }
   // work list: n descriptors followed by n tile starts
   const size_t tab = static_cast<size_t>(n) * sizeof(FrameArgs);
@@ -470,6 +475,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     l.first = d_first;
     l.n_streams = static_cast<uint32_t>(n);
     l.measure = measure;
+    l.stream = streams_rows(hot);
     e = launch_batch(x->M, x->dtype, l, x->s_compute);
   }
   // copy-out of the masks not written in place: the arena in one copy, scattered by the completion
@@ -549,6 +555,7 @@ gmm_status gmm_exec_create_stream(gmm_exec* x, const gmm_config* cfg, void* mem,
   }
   h->last_stream = x->s_compute;
   x->attached[h] = a;
+  x->hot += hot_bytes(h);
   x->M = h->cfg.M;
   x->dtype = h->cfg.state_dtype;
   *out = h;
@@ -563,6 +570,7 @@ gmm_status gmm_exec_destroy_stream(gmm_exec* x, gmm_handle* h) {
   if (it == x->attached.end()) return fail(GMM_ERR_INVALID_ARG, "handle not attached");
   x->cv.wait(lk, [&] { return it->second.in_flight == 0; });  // its last frame has completed
   x->attached.erase(it);
+  x->hot -= hot_bytes(h);
   lk.unlock();
   delete h;
   return GMM_OK;

@@ -338,33 +338,31 @@ __device__ __forceinline__ void process_pixel(const FrameArgs& a, uint32_t p, in
 }
 
 // Pixels [t0, t0 + tile_px) of stream `a` (tile_px a multiple of BLOCK; the part past the
-// stream's end is skipped), BLOCK at a time, the stream's mode resolved once for the tile. A
-// batched launch serves many streams, whose state together far exceeds the caches: its rows and
-// frames stream (kStream).
-template <int M, typename S, int MODE, int BLOCK, bool MEASURE>
+// stream's end is skipped), BLOCK at a time, the stream's mode resolved once for the tile.
+template <int M, typename S, int MODE, int BLOCK, int CP, bool MEASURE>
 __device__ __forceinline__ void process_tile_mode(const FrameArgs& a, uint32_t t0, uint32_t tile_px, int lane,
                                                   uint32_t* lds_wave) {
   for (uint32_t sub = 0; sub < tile_px; sub += BLOCK) {
     const uint32_t base = t0 + sub;
     if (base >= a.npix) break;  // uniform: the rest of the tile is past the stream's end
-    process_pixel<M, S, MODE, kStream, MEASURE>(a, base + threadIdx.x, lane, lds_wave);
+    process_pixel<M, S, MODE, CP, MEASURE>(a, base + threadIdx.x, lane, lds_wave);
   }
 }
 
-template <int M, typename S, int BLOCK, bool MEASURE>
+template <int M, typename S, int BLOCK, int CP, bool MEASURE>
 __device__ __forceinline__ void process_tile(const FrameArgs& a, uint32_t t0, uint32_t tile_px, int lane,
                                              uint32_t* lds_wave) {
   constexpr int RGBD = kModeRGB | kModeDepth, FUSED = RGBD | kModeFuse, DN = kFramesDense;
   const bool dense = ((a.mode & kModeRGB) == 0 || a.rgb_dense) && ((a.mode & kModeDepth) == 0 || a.depth_dense);
   switch (a.mode | (dense ? DN : 0)) {  // the modes a batch accepts
-    case FUSED | DN: process_tile_mode<M, S, FUSED | DN, BLOCK, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
-    case FUSED: process_tile_mode<M, S, FUSED, BLOCK, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
-    case RGBD | DN: process_tile_mode<M, S, RGBD | DN, BLOCK, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
-    case RGBD: process_tile_mode<M, S, RGBD, BLOCK, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
-    case kModeRGB | DN: process_tile_mode<M, S, kModeRGB | DN, BLOCK, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
-    case kModeRGB: process_tile_mode<M, S, kModeRGB, BLOCK, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
-    case kModeDepth | DN: process_tile_mode<M, S, kModeDepth | DN, BLOCK, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
-    case kModeDepth: process_tile_mode<M, S, kModeDepth, BLOCK, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
+    case FUSED | DN: process_tile_mode<M, S, FUSED | DN, BLOCK, CP, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
+    case FUSED: process_tile_mode<M, S, FUSED, BLOCK, CP, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
+    case RGBD | DN: process_tile_mode<M, S, RGBD | DN, BLOCK, CP, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
+    case RGBD: process_tile_mode<M, S, RGBD, BLOCK, CP, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
+    case kModeRGB | DN: process_tile_mode<M, S, kModeRGB | DN, BLOCK, CP, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
+    case kModeRGB: process_tile_mode<M, S, kModeRGB, BLOCK, CP, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
+    case kModeDepth | DN: process_tile_mode<M, S, kModeDepth | DN, BLOCK, CP, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
+    case kModeDepth: process_tile_mode<M, S, kModeDepth, BLOCK, CP, MEASURE>(a, t0, tile_px, lane, lds_wave); break;
     default: break;
   }
 }

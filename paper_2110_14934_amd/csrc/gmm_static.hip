@@ -156,6 +156,7 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
   for (int32_t i = 1; i < n; ++i)
     if (sorted[i] == sorted[i - 1]) return fail(GMM_ERR_INVALID_ARG, "a handle appears twice");
   uint64_t total = 0, pixels = 0;
+  size_t hot = 0;
   for (int32_t i = 0; i < n; ++i) {
     gmm_handle* h = handles[i];
     const gmm_stream_io& s = io[i];
@@ -171,6 +172,7 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
     }
     total += (static_cast<uint64_t>(h->npix) + t.tile_pixels - 1) / t.tile_pixels;
     pixels += static_cast<uint64_t>(h->npix);
+    hot += hot_bytes(h);
   }
   if (total >= (1ull << 31)) return fail(GMM_ERR_INVALID_ARG, "too many tiles in one launch");
   const int dev = handles[0]->cfg.device;
@@ -210,6 +212,7 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
   l.first = first;
   l.n_streams = static_cast<uint32_t>(n);
   l.measure = measure;
+  l.stream = streams_rows(hot);
   e = launch_batch(handles[0]->cfg.M, handles[0]->cfg.state_dtype, l, hs);
   if (e != hipSuccess) return hip_fail(e, "static batch kernel launch");
   for (int32_t i = 0; i < n; ++i) handles[i]->last_stream = hs;
