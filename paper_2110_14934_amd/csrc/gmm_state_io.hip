@@ -14,7 +14,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cmath>
 #include <mutex>
 
 #include "gmm.h"
@@ -265,13 +264,16 @@ gmm_status gmm_write_state(gmm_handle* h, const double* host_in, void* stream) {
   size_t params = 0;
   for (int i = 0; i < nm; ++i) params += static_cast<size_t>(models[i].C + 2) * M * n;
   const double* fuse_in = host_in + params;
-  if (sep_both(h)) {
+  if (sep_both(h)) {  // no early exit and no call: the loop vectorises
+    int bad_bit = 0, bad_count = 0;
     for (uint32_t i = 0; i < n; ++i) {
       const double I = fuse_in[i], c = fuse_in[static_cast<size_t>(n) + i];
-      if (!(I == 0.0 || I == 1.0)) return fail(GMM_ERR_INVALID_ARG, "fusion bit I must be 0 or 1");
-      if (!(c == std::floor(c) && c >= -3.0 && c <= 3.0))
-        return fail(GMM_ERR_INVALID_ARG, "fusion counter cpt must be an integer in [-3, 3]");
+      const double r = c >= -3.0 && c <= 3.0 ? c : 0.5;  // 0.5: not an integer
+      bad_bit |= !(I == 0.0 || I == 1.0);
+      bad_count |= r != static_cast<double>(static_cast<int>(r));
     }
+    if (bad_bit) return fail(GMM_ERR_INVALID_ARG, "fusion bit I must be 0 or 1");
+    if (bad_count) return fail(GMM_ERR_INVALID_ARG, "fusion counter cpt must be an integer in [-3, 3]");
   }
   DeviceGuard g(h->cfg.device);
   if (!g.ok()) return fail(GMM_ERR_DEVICE, "cannot select the handle's device");
