@@ -466,9 +466,12 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     e = hipEventRecord(s.h2d_done[c], x->s_in[c]);
     if (e == hipSuccess) e = hipStreamWaitEvent(x->s_compute, s.h2d_done[c], 0);
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(s.d_table, s.h_table, bytes, hipMemcpyHostToDevice, x->s_compute);
-  const FrameArgs* d_tab = static_cast<const FrameArgs*>(s.d_table);
-  const uint32_t* d_first = reinterpret_cast<const uint32_t*>(static_cast<const char*>(s.d_table) + tab);
+  FrameArgs* d_tab = static_cast<FrameArgs*>(s.d_table);
+  uint32_t* d_first = reinterpret_cast<uint32_t*>(static_cast<char*>(s.d_table) + tab);
+  if (e == hipSuccess)
+    e = static_cast<size_t>(n) <= kPackStreams
+            ? pack_descriptors(s.h_table, h_first, n, d_tab, d_first, x->s_compute)
+            : hipMemcpyAsync(s.d_table, s.h_table, bytes, hipMemcpyHostToDevice, x->s_compute);
   if (e == hipSuccess) {
     BatchLaunch l = batch_launch(tun, open, static_cast<uint32_t>(total_tiles), pixels, x->cu_count);
     l.table = d_tab;

@@ -3,17 +3,15 @@
 // gmm_batch_apply keeps each batch's stream descriptors and first tiles in device memory that
 // gmm_batch_create allocates. This entry point takes the handles directly and keeps the same
 // per-call tables in one file-scope device array instead (`scratch`, below): the descriptors of
-// up to kStaticMaxStreams streams and each stream's first tile. They reach the device through
-// small pack kernels whose arguments carry up to kPackPerLaunch streams each (kernel arguments are
-// captured by value, so no host buffer has to outlive the call), and the batched kernel runs on
-// them, so results are bit-identical to gmm_batch_apply.
+// up to kStaticMaxStreams streams and each stream's first tile. They reach the device as kernel
+// arguments (pack_descriptors), so no host buffer has to outlive the call, and the batched kernel
+// runs on them, so results are bit-identical to gmm_batch_apply.
 //
 // The array is one per device and shared by every call on that device: calls that overlap on one
 // device (different streams, or different host threads without ordering) race on it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstring>
 #include <mutex>
 #include <string>
 
@@ -29,73 +27,6 @@ static_assert(kTableBytes % 256 == 0, "the first-tile array starts 256-byte alig
 
 // [descriptors: kStaticMaxStreams x FrameArgs][first tile of each stream: kStaticMaxStreams x u32]
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
-
-// What differs from stream to stream of a descriptor. The model constants of a launch are sent once
-// (streams of one call nearly always share them; a stream with others starts another launch), which
-// lets the 4 KB of a kernel's arguments carry 32 streams; with whole descriptors they carry 16.
-struct PackEntry {
-  uint32_t npix, width, mode;
-  uint32_t dense;  // bit 0 rgb_dense, bit 1 depth_dense
-  const uint8_t* rgb;
-  int64_t rgb_pitch;
-  const uint16_t* depth;
-  int64_t depth_pitch;
-  void* st_rgb;
-  void* st_depth;
-  uint8_t* fstate;
-  uint64_t* fg_rgb;
-  uint64_t* fg_depth;
-  uint64_t* fused;
-  uint64_t* wave_bytes;
-};
-
-constexpr int kPackPerLaunch = 32;
-struct PackArgs {
-  PackEntry e[kPackPerLaunch];
-  uint32_t first[kPackPerLaunch];
-  ModelConsts kc, kd;
-  uint32_t base;   // index of e[0] in the tables
-  uint32_t count;  // entries used
-};
-static_assert(sizeof(PackArgs) + 2 * sizeof(void*) <= 4096, "kernel arguments");
-
-static PackEntry pack_entry(const FrameArgs& a) {
-  return PackEntry{static_cast<uint32_t>(a.npix), static_cast<uint32_t>(a.width), static_cast<uint32_t>(a.mode),
-                   (a.rgb_dense ? 1u : 0u) | (a.depth_dense ? 2u : 0u), a.rgb, a.rgb_pitch, a.depth, a.depth_pitch,
-                   a.st_rgb, a.st_depth, a.fstate, a.fg_rgb, a.fg_depth, a.fused, a.wave_bytes};
-}
-
-// A launch costs its latency (~1.7 us on the GPU, ~3.5 us of the caller's time), so what counts is
-// how many there are: 24 small streams take one (three of 8 whole descriptors before: 25.2 -> 21.4
-// us a call).
-__global__ void __launch_bounds__(64) pack_kernel(PackArgs p, FrameArgs* __restrict__ table,
-                                                  uint32_t* __restrict__ first) {
-  const uint32_t i = threadIdx.x;
-  if (i >= p.count) return;
-  const PackEntry e = p.e[i];
-  FrameArgs a{};
-  a.npix = e.npix;
-  a.tiles64 = (e.npix + kWave - 1) / kWave;
-  a.width = static_cast<int32_t>(e.width);
-  a.rgb_dense = static_cast<int32_t>(e.dense & 1u);
-  a.depth_dense = static_cast<int32_t>(e.dense >> 1);
-  a.rgb = e.rgb;
-  a.rgb_pitch = e.rgb_pitch;
-  a.depth = e.depth;
-  a.depth_pitch = e.depth_pitch;
-  a.st_rgb = e.st_rgb;
-  a.st_depth = e.st_depth;
-  a.fstate = e.fstate;
-  a.fg_rgb = e.fg_rgb;
-  a.fg_depth = e.fg_depth;
-  a.fused = e.fused;
-  a.kc = p.kc;
-  a.kd = p.kd;
-  a.mode = static_cast<int32_t>(e.mode);
-  a.wave_bytes = e.wave_bytes;
-  table[p.base + i] = a;
-  first[p.base + i] = p.first[i];
-}
 
 // Per device: the device address of `scratch` (from hipGetSymbolAddress, taken once with the
 // device current; the array's name in host code is not a device address) and the CU count.
@@ -188,23 +119,19 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
   hipError_t e = hipSuccess;
   uint32_t next_first = 0;
   bool measure = false;
-  for (int32_t b = 0; b < n && e == hipSuccess;) {
-    PackArgs p{};
-    p.base = static_cast<uint32_t>(b);
-    p.kc = handles[b]->kc;
-    p.kd = handles[b]->kd;
-    for (; b < n && p.count < kPackPerLaunch; ++b, ++p.count) {
-      gmm_handle* h = handles[b];
-      if (std::memcmp(&h->kc, &p.kc, sizeof(p.kc)) != 0 || std::memcmp(&h->kd, &p.kd, sizeof(p.kd)) != 0) break;
-      const gmm_stream_io& s = io[b];
-      const FrameArgs a = frame_args(h, s.rgb, s.rgb_pitch_bytes, s.depth, s.depth_pitch_bytes, s.fg_rgb, s.fg_depth, s.fused);
-      p.e[p.count] = pack_entry(a);
-      measure = measure || a.wave_bytes != nullptr;
-      p.first[p.count] = next_first;
+  for (int32_t b = 0; b < n && e == hipSuccess; b += kPackPerLaunch) {
+    FrameArgs a[kPackPerLaunch];
+    uint32_t f[kPackPerLaunch];
+    const int32_t count = std::min(kPackPerLaunch, n - b);
+    for (int32_t i = 0; i < count; ++i) {
+      gmm_handle* h = handles[b + i];
+      const gmm_stream_io& s = io[b + i];
+      a[i] = frame_args(h, s.rgb, s.rgb_pitch_bytes, s.depth, s.depth_pitch_bytes, s.fg_rgb, s.fg_depth, s.fused);
+      measure = measure || a[i].wave_bytes != nullptr;
+      f[i] = next_first;
       next_first += static_cast<uint32_t>((h->npix + t.tile_pixels - 1) / t.tile_pixels);
     }
-    pack_kernel<<<1, 64, 0, hs>>>(p, table, first);
-    e = hipGetLastError();
+    e = pack_descriptors(a, f, count, table + b, first + b, hs);
   }
   if (e != hipSuccess) return hip_fail(e, "descriptor pack kernel launch");
   BatchLaunch l = batch_launch(t, tuning == nullptr, static_cast<uint32_t>(total), pixels, cus);

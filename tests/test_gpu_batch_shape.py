@@ -65,8 +65,12 @@ def test_default_pieces_cover_every_pixel(extra, dtype):
     _check(sizes + extra, "apply", dtype)
 
 
-# the static call sends the model constants once per group of equal ones: none alike, and groups
-# that end inside and at the end of a launch's 32 streams
-@pytest.mark.parametrize("n,alphas", [(40, (0.05, 0.02)), (70, (0.05,) * 32 + (0.02,) * 5), (33, (0.05,) * 32 + (0.1,))])
-def test_static_streams_keep_their_own_constants(n, alphas):
-    _check([(65 + i, 3) for i in range(n)], "static", "f16", alphas=alphas)
+# descriptors travel as kernel arguments, the model constants once per run of equal ones: none alike,
+# short and long runs, runs that end inside and at the end of a launch's 32 (16) streams, and the
+# largest batch that goes this way with its neighbours
+@pytest.mark.parametrize("call", ["apply", "static"])
+@pytest.mark.parametrize("n,alphas", [(40, (0.05, 0.02)), (70, (0.05,) * 32 + (0.02,) * 5), (33, (0.05,) * 32 + (0.1,)),
+                                      (17, (0.05,) * 3 + (0.1,)), (32, (0.05,)), (63, (0.05,)), (64, (0.05,)),
+                                      (65, (0.05,)), (64, (0.05,) * 20 + (0.1,) * 12)])
+def test_streams_keep_their_own_descriptors(n, alphas, call):
+    _check([(65 + i, 3) for i in range(n)], call, "f16", alphas=alphas)
