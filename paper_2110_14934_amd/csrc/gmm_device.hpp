@@ -325,16 +325,18 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // kStream marks them non-temporal: a frame streams through every row once, and rows far larger
 // than the caches would otherwise evict from them the lines that the general path's scattered
 // suffix accesses and the frames could still hit. Rows that fit in the last-level cache keep the
-// default policy for loads, so that they stay there from frame to frame, and are written through
-// the XCD's L2 (device scope) as the frame runs: the L2s are written back at the end of a kernel
-// in any case, and rows left dirty in them lengthen it (one VGA stream 7.9 -> 7.7 us, 1920x1080
-// colour in fp16 16.0 -> 14.7 us, four VGA streams in a batch 23.5 -> 21.3 us). Written through,
-// the suffixes' scattered pieces cost more than that (a frame in which every pixel writes one
-// took a fifth longer), so they stay with the L2.
+// default policy for loads, so that they stay there from frame to frame, and a wave whose lanes
+// all stayed on the fast path writes them through the XCD's L2 (device scope): the L2s are written
+// back at the end of a kernel in any case, and rows left dirty in them lengthen it (one VGA stream
+// 7.3 -> 6.5 us with the branch of step_store, 1920x1080 colour in fp16 16.0 -> 14.6 us, four VGA
+// streams in a batch 23.5 -> 21.3 us). A wave that also writes suffix pieces leaves both to the L2,
+// which merges the pieces: with its rows written through, a VGA clip in which most waves are such
+// waves took 10.9 instead of 10.5 us a frame, and with the pieces too a frame in which every pixel
+// writes one took a fifth longer.
 constexpr int kCached = 0;
 constexpr int kStream = 2;         // nt
-constexpr int kWriteThrough = 16;  // sc1: the row stores of kCached
-constexpr int row_store_policy(int cp) { return cp == kCached ? kWriteThrough : cp; }
+constexpr int kWriteThrough = 16;  // sc1: the row stores of a wave on the fast path, with kCached
+constexpr int fast_store_policy(int cp) { return cp == kCached ? kWriteThrough : cp; }
 
 // One lane's words of a row (W bytes), moved by one buffer instruction of that width.
 template <uint32_t W>
@@ -510,7 +512,7 @@ __device__ __forceinline__ void write_row(const Mix<M, C>& m, const StateBlock& 
     constexpr int k = RGBD_I(k_);
     o.w[k] = BufIO<S>::word(value_or_pad<M, C, S, v0 + k * vpw>(m), value_or_pad<M, C, S, v0 + k * vpw + vpw - 1>(m));
   });
-  store_row<W, row_store_policy(CP)>(o, b.rsrc, at_if(on, base + off + lane * W));
+  store_row<W, CP>(o, b.rsrc, at_if(on, base + off + lane * W));
 }
 
 // Values [0, LIMIT) of pixel p, straight into the Mix (see value_read for what comes along). A

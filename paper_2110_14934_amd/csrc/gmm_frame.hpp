@@ -108,13 +108,18 @@ __device__ __forceinline__ void load_prefix(Mix<M, C>& m, const StateBlock& blk,
 // pixel; `active` lanes update it (a depth hole is valid but not active: in the direct form it
 // writes back what it read; in the scaled form it rescales its weights to the tile's new scale,
 // hold_step). In the scaled form the tile's first lane then writes the new scale.
-// In three parts, and every load and store is issued by every lane (a lane with nothing to move
-// uses an offset outside the block), so no branch hides a memory instruction from the count the
-// compiler keeps for its waits: step_begin runs fast_step and issues the loads of the rest of
-// the state (their results are used only by lanes that take the general path); step_compute
-// runs the general step on those lanes; step_store writes back. The caller issues the other
-// modality's step_begin before this one's step_store, so that a wait for one modality's loads
-// never waits for the other's stores.
+// In three parts: step_begin runs fast_step and issues the loads of the rest of the state (their
+// results are used only by lanes that take the general path); step_compute runs the general step
+// on those lanes; step_store writes back. The caller issues the other modality's step_begin before
+// this one's step_store, so that a wait for one modality's loads never waits for the other's
+// stores. A load or store is issued by every lane (one with nothing to move uses an offset outside
+// the block), so that no per-lane branch hides a memory instruction from the count the compiler
+// keeps for its waits. A wave without any general-path lane skips the suffix stores, and their
+// address and packing arithmetic, by a branch the whole wave takes: they are the larger part of
+// the instructions of such a wave, and the loads the count matters for are behind them (VGA stream
+// 7.3 -> 6.8 us, 64 uneven fp32 streams 313 -> 305 us). In the direct form it skips the suffix loads
+// too (32 VGA fp16 streams 137.7 -> 135.9 us; in the scaled form the waits this costs outweigh it,
+// 306 -> 323 us).
 template <int M, int C, typename S>
 struct StepState {
   Mix<M, C> full;  // the whole state as read (general-path lanes)
@@ -148,7 +153,7 @@ __device__ __forceinline__ void step_begin(Mix<M, C>& m, StepState<M, C, S>& st,
   const bool fast = active && fast_step<M, C, SC>(m, x, k);
   st.slow = SC ? valid && !fast && !held : active && !fast;
   st.kout = held ? kin + 1 : kin;
-  load_rest<M, C, S, kFastLoad<M, C, S>, CP>(st.full, blk, p, st.slow);
+  if (SC || __ballot(st.slow) != 0) load_rest<M, C, S, kFastLoad<M, C, S>, CP>(st.full, blk, p, st.slow);
 }
 
 template <int M, int C, typename S>
@@ -201,9 +206,13 @@ __device__ __forceinline__ void step_store(const Mix<M, C>& m, const StepState<M
   // otherwise the suffix, are the general path's alone; of the suffix, a lane whose updated
   // component kept its rank writes only the pieces holding that rank.
   constexpr bool kSuffixShared = SF > NR;
-  store_mix<M, C, S, SF, true, kSuffixShared, CP>(m, blk, p, valid);
-  if constexpr (rows_from_exist<M, C, SF, S>()) store_rows_from<M, C, S, SF, CP>(m, blk, p, slow);
-  if constexpr (!kSuffixShared) store_suffix_of<M, C, S>(m, blk, p, slow, kept < 0, kept);
+  if (__ballot(slow) != 0) {
+    store_mix<M, C, S, SF, true, kSuffixShared, CP>(m, blk, p, valid);
+    if constexpr (rows_from_exist<M, C, SF, S>()) store_rows_from<M, C, S, SF, CP>(m, blk, p, slow);
+    if constexpr (!kSuffixShared) store_suffix_of<M, C, S>(m, blk, p, slow, kept < 0, kept);
+  } else {
+    store_mix<M, C, S, SF, true, kSuffixShared, fast_store_policy(CP)>(m, blk, p, valid);
+  }
   if constexpr (SC) {  // the tile's new scale, from its first lane
     store_scale(st.gnext, blk, p, valid && (p & 63u) == 0);
     wave_bytes += 8u;
