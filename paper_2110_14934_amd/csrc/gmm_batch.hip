@@ -43,7 +43,9 @@ __device__ __forceinline__ uint32_t find_stream(const uint32_t* __restrict__ fir
   return lo;
 }
 
-// Five waves per SIMD: the body fits them without spilling (checked at build time by the tests).
+// Five waves per SIMD, six at M <= 3: the body fits them without spilling (checked at build time by
+// the tests; 24 small streams at M = 3 take 16.9 us with the five it would have at 82 registers,
+// 16.2 with six).
 // A block takes one piece of a tile (tile_px >> piece_shift pixels) and the grid usually has a
 // block for every piece (batch_launch below); a smaller grid walks the pieces b, b+G, b+2G, ...
 // CP: the cache policy of the rows (kCached or kStream; streams_rows).
@@ -51,7 +53,7 @@ __device__ __forceinline__ uint32_t find_stream(const uint32_t* __restrict__ fir
 // takes it (with kStream) only when a stream of the batch has one, so the common body never forms
 // the counts.
 template <int M, typename S, int BLOCK, int CP, bool MEASURE>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5))) batch_kernel(const FrameArgs* __restrict__ table,
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(M <= 3 ? 6 : 5))) batch_kernel(const FrameArgs* __restrict__ table,
                                                       const uint32_t* __restrict__ first, uint32_t n_streams,
                                                       uint32_t n_pieces, uint32_t tile_px, uint32_t piece_shift) {
   __shared__ uint32_t lds[BLOCK / kWave][48];

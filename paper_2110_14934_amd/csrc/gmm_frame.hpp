@@ -101,9 +101,8 @@ __device__ __forceinline__ void load_prefix(Mix<M, C>& m, const StateBlock& blk,
 // fast_step is the step specialised to the case above; a lane for which that case holds writes
 // back only the values that case changes (the weights and rank 0, or rank 0 alone). Any other
 // lane keeps the prefix as read, loads the rest of its state, runs the full step from the
-// original values and writes back what changed: the hot rows, and the whole suffix when the
-// ranks were reordered (or every scaled weight changed), else only the suffix pieces of the rank
-// the updated component kept. fast_step computes exactly what the full step
+// original values and writes back what changed: the hot rows, and the suffix pieces of the ranks
+// between the updated component's old and new place (every piece when every scaled weight changed). fast_step computes exactly what the full step
 // computes for such a pixel, so results never depend on which path ran. `valid` lanes hold a
 // pixel; `active` lanes update it (a depth hole is valid but not active: in the direct form it
 // writes back what it read; in the scaled form it rescales its weights to the tile's new scale,
@@ -126,7 +125,7 @@ struct StepState {
   bool slow;       // this lane takes the general path
   bool fold;       // the tile's scale folds this frame (scaled form; uniform over the wave)
   bool fg;         // its foreground bit
-  int kept;        // the rank its updated component kept, or -1 when the ranks were reordered
+  uint32_t changed;  // bit r: rank r's values changed (slow lanes)
   uint32_t kout;   // the pixel's hole count after the frame (scaled form)
   float gnext;     // the tile's scale after the frame (scaled form)
 };
@@ -161,10 +160,9 @@ __device__ __forceinline__ void step_compute(Mix<M, C>& m, StepState<M, C, S>& s
                                              const ModelConsts& k) {
   constexpr bool SC = kScaled<S>;
   st.fg = false;
-  st.kept = -1;
+  st.changed = 0;
   if (st.slow) {  // no memory access in here
-    int j = M, q = M;
-    bool all = true;
+    st.changed = (1u << M) - 1u;
     if (SC && !active) {
       if constexpr (SC) hold_step<M, C>(st.full, k);
     } else {
@@ -173,13 +171,15 @@ __device__ __forceinline__ void step_compute(Mix<M, C>& m, StepState<M, C, S>& s
       bool done = false;
       if constexpr (SC && M > 1) done = rank1_step<M, C>(st.full, x, k, st.fg);
       if (done) {
-        j = q = 1;
-        all = false;
+        st.changed = 2u;
       } else {
+        int j = M, q = M;
+        bool all = true;
         st.fg = mix_step<M, C, SC>(st.full, x, k, j, q, all);
+        const int t = min(j, M - 1);  // the updated component's old place; q is its new one
+        if (!all) st.changed = (2u << max(t, q)) - (1u << min(t, q));
       }
     }
-    st.kept = !all && (j < M ? j : M - 1) == q ? q : -1;
     // hold_step and a fold leave the weights relative to the tile's scale alone
     if (!active || st.fold) st.kout = 0;
     m = st.full;
@@ -198,18 +198,18 @@ __device__ __forceinline__ void step_store(const Mix<M, C>& m, const StepState<M
   constexpr int NR = static_cast<int>(P::nf);  // values held by the hot rows
   constexpr bool SC = kScaled<S>;
   const bool slow = st.slow;
-  const int kept = st.kept;
+  const uint32_t changed = st.changed;
   // Write-back: every piece both paths write goes out in one store for all the lanes that write
   // it (a hot row then leaves the wave as one write, not as one per path). Both paths write the
   // rows the fast store covers; when the fast store reaches into the suffix (the rows cannot
   // hold the prefix), both write the suffix too. Rows past the fast store, and
-  // otherwise the suffix, are the general path's alone; of the suffix, a lane whose updated
-  // component kept its rank writes only the pieces holding that rank.
+  // otherwise the suffix, are the general path's alone; of the suffix, a lane writes only the
+  // pieces holding a rank that changed.
   constexpr bool kSuffixShared = SF > NR;
   if (__ballot(slow) != 0) {
     store_mix<M, C, S, SF, true, kSuffixShared, CP>(m, blk, p, valid);
     if constexpr (rows_from_exist<M, C, SF, S>()) store_rows_from<M, C, S, SF, CP>(m, blk, p, slow);
-    if constexpr (!kSuffixShared) store_suffix_of<M, C, S>(m, blk, p, slow, kept < 0, kept);
+    if constexpr (!kSuffixShared) store_suffix_of<M, C, S>(m, blk, p, changed, wave_bytes);
   } else {
     store_mix<M, C, S, SF, true, kSuffixShared, fast_store_policy(CP)>(m, blk, p, valid);
   }
@@ -223,12 +223,8 @@ __device__ __forceinline__ void step_store(const Mix<M, C>& m, const StepState<M
   if constexpr (kSuffixShared) {
     wave_bytes += n_slow * 2u * kFull;
   } else {
-    // read everything; write the rows, and the whole suffix or rank `kept`'s pieces of it
-    wave_bytes += n_slow * (kFull + P::hot) + __popcll(__ballot(slow && kept < 0)) * P::sb;
-    static_for<0, M>([&](auto r_) RGBD_BODY {
-      constexpr int r = RGBD_I(r_);
-      wave_bytes += __popcll(__ballot(slow && kept == r)) * suffix_rank_bytes<M, C, S>(r);
-    });
+    // read everything; write the rows and the changed pieces of the suffix (store_suffix_of)
+    wave_bytes += n_slow * (kFull + P::hot);
   }
 }
 
