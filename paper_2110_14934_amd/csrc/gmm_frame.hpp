@@ -26,14 +26,13 @@ struct RgbLoad {
 // bytes, with no row arithmetic and no per-stream test.
 constexpr int kFramesDense = 16;
 
-template <int CP = kCached, bool DENSE = false>
+template <bool DENSE = false>
 __device__ __forceinline__ RgbLoad issue_rgb_pixel(const FrameArgs& a, uint32_t p, uint32_t wave_base, int lane) {
   RgbLoad r{};
   r.staged = (DENSE || a.rgb_dense) && (wave_base + kWave <= a.npix);
   if (r.staged) {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(a.rgb + 3 * static_cast<uint64_t>(wave_base));
-    if constexpr (CP == kStream) r.w = __builtin_nontemporal_load(&src[lane < 48 ? lane : 47]);
-    else r.w = src[lane < 48 ? lane : 47];
+    r.w = src[lane < 48 ? lane : 47];
   } else {
     const uint8_t* b;
     if constexpr (DENSE) {
@@ -66,12 +65,9 @@ __device__ __forceinline__ void finish_rgb_pixel(const RgbLoad& r, int lane, uin
   }
 }
 
-template <int CP = kCached, bool DENSE = false>
+template <bool DENSE = false>
 __device__ __forceinline__ float load_depth_pixel(const FrameArgs& a, uint32_t p) {
-  if (DENSE || a.depth_dense) {
-    if constexpr (CP == kStream) return static_cast<float>(__builtin_nontemporal_load(&a.depth[p]));
-    else return static_cast<float>(a.depth[p]);
-  }
+  if (DENSE || a.depth_dense) return static_cast<float>(a.depth[p]);
   const uint32_t y = p / static_cast<uint32_t>(a.width);
   const uint32_t xx = p - y * static_cast<uint32_t>(a.width);
   const uint16_t* row = reinterpret_cast<const uint16_t*>(
@@ -267,8 +263,8 @@ __device__ __forceinline__ void process_pixel(const FrameArgs& a, uint32_t p, in
     const StateBlock blk = make_block<M, 4, S>(a.st_rgb, a.tiles64);
     Mix<M, 4> m;
     const uint32_t pc = valid ? p : a.npix - 1;
-    const RgbLoad rl = issue_rgb_pixel<CP>(a, pc, wave_base, lane);
-    const uint32_t d = static_cast<uint32_t>(load_depth_pixel<CP>(a, pc));
+    const RgbLoad rl = issue_rgb_pixel<>(a, pc, wave_base, lane);
+    const uint32_t d = static_cast<uint32_t>(load_depth_pixel<>(a, pc));
     load_prefix<M, 4, S, CP>(m, blk, pc, true);
     float x3[3];
     finish_rgb_pixel(rl, lane, lds_wave, x3);
@@ -292,8 +288,8 @@ __device__ __forceinline__ void process_pixel(const FrameArgs& a, uint32_t p, in
   const uint32_t pc = valid ? p : a.npix - 1;
   constexpr bool dense = (MODE & kFramesDense) != 0;
   RgbLoad rl{};
-  if (do_c) rl = issue_rgb_pixel<CP, dense>(a, pc, wave_base, lane);
-  const float xd = do_d ? load_depth_pixel<CP, dense>(a, pc) : 0.f;
+  if (do_c) rl = issue_rgb_pixel<dense>(a, pc, wave_base, lane);
+  const float xd = do_d ? load_depth_pixel<dense>(a, pc) : 0.f;
   // the flags byte: List 1 state (bits 0-3) and, in the scaled form, the depth hole count
   constexpr bool do_flags = do_f || (kScaled<S> && do_d);
   const uint32_t fst = do_flags ? a.fstate[pc] : 0u;

@@ -40,7 +40,7 @@ struct FrameArgs {
 enum FrameMode : int { kModeRGB = 1, kModeDepth = 2, kModeFuse = 4, kModeAug = 8 };
 
 // Launchers (return hipSuccess or the launch error).
-// `stream`: the kernel's rows and frames take the non-temporal cache policy (kStream), for streams
+// `stream`: the kernel's rows take the non-temporal cache policy (kStream), for streams
 // whose hot bytes cannot stay in the last-level cache between frames (streams_rows).
 hipError_t launch_frame(const FrameArgs& a, int M, int dtype, int mode, bool stream, hipStream_t s);
 hipError_t launch_fuse(const uint64_t* fr, const uint64_t* fd, uint64_t* out, uint8_t* fstate,
