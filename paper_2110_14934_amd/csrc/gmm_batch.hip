@@ -13,7 +13,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstring>
 #include <map>
 #include <mutex>
 #include <new>
@@ -23,25 +22,11 @@
 #include <vector>
 
 #include "gmm.h"
+#include "gmm_batch.hpp"
 #include "gmm_frame.hpp"
 #include "gmm_internal.hpp"
 
 namespace rgbd {
-
-// The stream of tile t: the last entry of `first` (n entries, first[0] = 0, increasing) that is
-// <= t. A binary search in scalar registers: its loads hit the scalar cache that every block of
-// the CU reads `first` through, which a tile map of one word per tile does not (64 streams, fp32:
-// 312 us per launch either way), and a wave-wide probe of all entries at once, one vector load,
-// waits longer (321 us).
-__device__ __forceinline__ uint32_t find_stream(const uint32_t* __restrict__ first, uint32_t n, uint32_t t) {
-  uint32_t lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi + 1) >> 1;
-    if (first[mid] <= t) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
 
 // Five waves per SIMD, six at M <= 3: the body fits them without spilling (checked at build time by
 // the tests; 24 small streams at M = 3 take 16.9 us with the five it would have at 82 registers,
@@ -134,46 +119,12 @@ BatchLaunch batch_launch(const gmm_batch_tuning& t, bool open, uint32_t n_tiles,
   return l;
 }
 
-// What differs from stream to stream of a descriptor. Streams of one call nearly always share the
-// model constants; sent once per launch, they let the 4 KB of a kernel's arguments carry 32
-// streams, where whole descriptors fill them with 16.
-struct PackEntry {
-  uint32_t npix, width, mode;
-  uint32_t dense;  // bit 0 rgb_dense, bit 1 depth_dense
-  const uint8_t* rgb;
-  int64_t rgb_pitch;
-  const uint16_t* depth;
-  int64_t depth_pitch;
-  void* st_rgb;
-  void* st_depth;
-  uint8_t* fstate;
-  uint64_t* fg_rgb;
-  uint64_t* fg_depth;
-  uint64_t* fused;
-  uint64_t* wave_bytes;
-};
-
-struct PackArgs {
-  PackEntry e[kPackPerLaunch];
-  uint32_t first[kPackPerLaunch];
-  ModelConsts kc, kd;
-  uint32_t base;   // index of e[0] in the tables
-  uint32_t count;  // entries used
-};
-static_assert(sizeof(PackArgs) + 2 * sizeof(void*) <= 4096, "kernel arguments");
-
 struct PackWholeArgs {
   FrameArgs a[kPackPerLaunch / 2];
   uint32_t first[kPackPerLaunch / 2];
   uint32_t base, count;
 };
 static_assert(sizeof(PackWholeArgs) + 2 * sizeof(void*) <= 4096, "kernel arguments");
-
-static PackEntry pack_entry(const FrameArgs& a) {
-  return PackEntry{static_cast<uint32_t>(a.npix), static_cast<uint32_t>(a.width), static_cast<uint32_t>(a.mode),
-                   (a.rgb_dense ? 1u : 0u) | (a.depth_dense ? 2u : 0u), a.rgb, a.rgb_pitch, a.depth, a.depth_pitch,
-                   a.st_rgb, a.st_depth, a.fstate, a.fg_rgb, a.fg_depth, a.fused, a.wave_bytes};
-}
 
 // A launch costs its latency (~1.7 us on the GPU, ~3.5 us of the caller's time), so what counts is
 // how many there are: 24 small streams take one (three of 8 whole descriptors before: 25.2 -> 21.4
@@ -182,28 +133,7 @@ __global__ void __launch_bounds__(64) pack_kernel(PackArgs p, FrameArgs* __restr
                                                   uint32_t* __restrict__ first) {
   const uint32_t i = threadIdx.x;
   if (i >= p.count) return;
-  const PackEntry e = p.e[i];
-  FrameArgs a{};
-  a.npix = e.npix;
-  a.tiles64 = (e.npix + kWave - 1) / kWave;
-  a.width = static_cast<int32_t>(e.width);
-  a.rgb_dense = static_cast<int32_t>(e.dense & 1u);
-  a.depth_dense = static_cast<int32_t>(e.dense >> 1);
-  a.rgb = e.rgb;
-  a.rgb_pitch = e.rgb_pitch;
-  a.depth = e.depth;
-  a.depth_pitch = e.depth_pitch;
-  a.st_rgb = e.st_rgb;
-  a.st_depth = e.st_depth;
-  a.fstate = e.fstate;
-  a.fg_rgb = e.fg_rgb;
-  a.fg_depth = e.fg_depth;
-  a.fused = e.fused;
-  a.kc = p.kc;
-  a.kd = p.kd;
-  a.mode = static_cast<int32_t>(e.mode);
-  a.wave_bytes = e.wave_bytes;
-  table[p.base + i] = a;
+  table[p.base + i] = unpack_entry(p, i);
   if (first) first[p.base + i] = p.first[i];
 }
 
@@ -220,20 +150,10 @@ hipError_t pack_descriptors(const FrameArgs* a, const uint32_t* first, int32_t n
   hipError_t e = hipSuccess;
   for (int32_t b = 0; b < n && e == hipSuccess;) {
     int32_t same = 1;  // streams from b on with b's constants
-    while (same < kPackPerLaunch && b + same < n && std::memcmp(&a[b + same].kc, &a[b].kc, sizeof(ModelConsts)) == 0 &&
-           std::memcmp(&a[b + same].kd, &a[b].kd, sizeof(ModelConsts)) == 0)
+    while (same < kPackPerLaunch && b + same < n && same_consts(a[b], a[b + same]))
       ++same;
     if (same >= kPackPerLaunch / 2 || b + same == n) {
-      PackArgs p{};
-      p.base = static_cast<uint32_t>(b);
-      p.count = static_cast<uint32_t>(same);
-      p.kc = a[b].kc;
-      p.kd = a[b].kd;
-      for (int32_t i = 0; i < same; ++i) {
-        p.e[i] = pack_entry(a[b + i]);
-        if (first) p.first[i] = first[b + i];
-      }
-      pack_kernel<<<1, 64, 0, s>>>(p, d_table, d_first);
+      pack_kernel<<<1, 64, 0, s>>>(pack_args(a + b, first ? first + b : nullptr, same, static_cast<uint32_t>(b)), d_table, d_first);
       b += same;
     } else {
       PackWholeArgs p{};

@@ -6,7 +6,7 @@
 // a transfer before the kernel and a submission per frame. A wave's 192 colour bytes and 128 depth
 // bytes are contiguous; such reads reach 57 GB/s over the host link, the rate of one large DMA copy
 // (per-frame DMA copies reach 47), and the kernel's arithmetic hides behind them. A tick of 16 streams (27 MB
-// of frames) took 841 us with copies to the device and back and takes 557 us; one 640x480 stream
+// of frames) took 841 us with copies to the device and back and takes 547 us; one 640x480 stream
 // 127 and 59 us.
 // Frames that are not page-locked, or not aligned for the kernel's loads, are copied to the
 // stream's device slot first (spread over four copy-in streams, so several DMA engines share the
@@ -466,20 +466,23 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     e = hipEventRecord(s.h2d_done[c], x->s_in[c]);
     if (e == hipSuccess) e = hipStreamWaitEvent(x->s_compute, s.h2d_done[c], 0);
   }
-  FrameArgs* d_tab = static_cast<FrameArgs*>(s.d_table);
-  uint32_t* d_first = reinterpret_cast<uint32_t*>(static_cast<char*>(s.d_table) + tab);
-  if (e == hipSuccess)
-    e = static_cast<size_t>(n) <= kPackStreams
-            ? pack_descriptors(s.h_table, h_first, n, d_tab, d_first, x->s_compute)
-            : hipMemcpyAsync(s.d_table, s.h_table, bytes, hipMemcpyHostToDevice, x->s_compute);
   if (e == hipSuccess) {
     BatchLaunch l = batch_launch(tun, open, static_cast<uint32_t>(total_tiles), pixels, x->cu_count);
-    l.table = d_tab;
-    l.first = d_first;
     l.n_streams = static_cast<uint32_t>(n);
     l.measure = measure;
     l.stream = streams_rows(hot);
-    e = launch_batch(x->M, x->dtype, l, x->s_compute);
+    if (fits_args(s.h_table, l)) {
+      e = launch_batch_args(x->M, x->dtype, s.h_table, h_first, l, x->s_compute);
+    } else {
+      FrameArgs* d_tab = static_cast<FrameArgs*>(s.d_table);
+      uint32_t* d_first = reinterpret_cast<uint32_t*>(static_cast<char*>(s.d_table) + tab);
+      l.table = d_tab;
+      l.first = d_first;
+      e = static_cast<size_t>(n) <= kPackStreams
+              ? pack_descriptors(s.h_table, h_first, n, d_tab, d_first, x->s_compute)
+              : hipMemcpyAsync(s.d_table, s.h_table, bytes, hipMemcpyHostToDevice, x->s_compute);
+      if (e == hipSuccess) e = launch_batch(x->M, x->dtype, l, x->s_compute);
+    }
   }
   // copy-out of the masks not written in place: the arena in one copy, scattered by the completion
   // thread

@@ -74,6 +74,12 @@ hipError_t launch_batch(int M, int dtype, const BatchLaunch& l, hipStream_t s);
 constexpr int kPackPerLaunch = 32;
 hipError_t pack_descriptors(const FrameArgs* a, const uint32_t* first, int32_t n, FrameArgs* d_table, uint32_t* d_first,
                             hipStream_t s);
+// Launches that need no table afterwards (the static call, ticks) carry the descriptors of up to
+// kPackPerLaunch streams with equal constants in the batched kernel's own arguments; fits_args says
+// whether `l` may. 24 small streams 21.8 -> 18.1 us a static call.
+bool fits_args(const FrameArgs* a, const BatchLaunch& l);
+hipError_t launch_batch_args(int M, int dtype, const FrameArgs* a, const uint32_t* first, const BatchLaunch& l,
+                             hipStream_t s);
 // Up to this many streams a batch's or a tick's descriptors go that way, above it in one copy from
 // page-locked memory. gmm_batch_apply on small streams, arguments against copy: 1 stream 8.9 and
 // 14.6 us, 32 streams 13.9 and 17.3 us, 33 streams (a second launch) 18.2 and 17.2 us.

@@ -16,6 +16,7 @@
 #include <string>
 
 #include "gmm.h"
+#include "gmm_batch.hpp"
 #include "gmm_internal.hpp"
 
 namespace rgbd {
@@ -27,6 +28,63 @@ static_assert(kTableBytes % 256 == 0, "the first-tile array starts 256-byte alig
 
 // [descriptors: kStaticMaxStreams x FrameArgs][first tile of each stream: kStaticMaxStreams x u32]
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
+
+// The batched kernel on descriptors in its own arguments: one launch instead of two where they fit,
+// which saves the pack kernel and the gap behind it. 256 threads a block, no byte counting.
+template <int M, typename S, int CP>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(M <= 3 ? 6 : 5))) batch_args_kernel(
+    PackArgs p, uint32_t n_pieces, uint32_t tile_px, uint32_t piece_shift) {
+  __shared__ uint32_t lds[kWavesPerBlock][48];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = threadIdx.x / kWave;
+  const uint32_t piece_px = tile_px >> piece_shift, part_mask = (1u << piece_shift) - 1u;
+  for (uint32_t b = blockIdx.x; b < n_pieces; b += gridDim.x) {
+    const uint32_t t = b >> piece_shift;
+    const uint32_t s = find_stream(p.first, p.count, t);
+    const FrameArgs a = unpack_entry(p, s);
+    const uint32_t t0 = (t - p.first[s]) * tile_px + (b & part_mask) * piece_px;
+    process_tile<M, S, kBlock, CP, false>(a, t0, piece_px, lane, lds[wv]);
+  }
+}
+
+template <int M, typename S>
+static hipError_t launch_args_ms(const PackArgs& p, const BatchLaunch& l, hipStream_t s) {
+  if (l.stream)
+    batch_args_kernel<M, S, kStream><<<dim3(l.grid), dim3(kBlock), 0, s>>>(p, l.n_pieces, l.tile_px, l.piece_shift);
+  else
+    batch_args_kernel<M, S, kCached><<<dim3(l.grid), dim3(kBlock), 0, s>>>(p, l.n_pieces, l.tile_px, l.piece_shift);
+  return hipGetLastError();
+}
+
+template <typename S>
+static hipError_t launch_args_s(int M, const PackArgs& p, const BatchLaunch& l, hipStream_t s) {
+  switch (M) {
+    case 1: return launch_args_ms<1, S>(p, l, s);
+    case 2: return launch_args_ms<2, S>(p, l, s);
+    case 3: return launch_args_ms<3, S>(p, l, s);
+    case 4: return launch_args_ms<4, S>(p, l, s);
+    case 5: return launch_args_ms<5, S>(p, l, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+bool fits_args(const FrameArgs* a, const BatchLaunch& l) {
+  if (l.n_streams > static_cast<uint32_t>(kPackPerLaunch) || l.measure || l.block != kBlock) return false;
+  for (uint32_t i = 1; i < l.n_streams; ++i)
+    if (!same_consts(a[0], a[i])) return false;
+  return true;
+}
+
+hipError_t launch_batch_args(int M, int dtype, const FrameArgs* a, const uint32_t* first, const BatchLaunch& l,
+                             hipStream_t s) {
+  const PackArgs p = pack_args(a, first, static_cast<int32_t>(l.n_streams), 0);
+  switch (dtype) {
+    case GMM_F32: return launch_args_s<float>(M, p, l, s);
+    case GMM_F16: return launch_args_s<f16s>(M, p, l, s);
+    case GMM_BF16: return launch_args_s<bf16s>(M, p, l, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 // Per device: the device address of `scratch` (from hipGetSymbolAddress, taken once with the
 // device current; the array's name in host code is not a device address) and the CU count.
@@ -118,7 +176,12 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
   hipStream_t hs = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   uint32_t next_first = 0;
-  bool measure = false;
+  BatchLaunch l = batch_launch(t, tuning == nullptr, static_cast<uint32_t>(total), pixels, cus);
+  l.table = table;
+  l.first = first;
+  l.n_streams = static_cast<uint32_t>(n);
+  l.stream = streams_rows(hot);
+  bool packed = true;
   for (int32_t b = 0; b < n && e == hipSuccess; b += kPackPerLaunch) {
     FrameArgs a[kPackPerLaunch];
     uint32_t f[kPackPerLaunch];
@@ -127,20 +190,18 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
       gmm_handle* h = handles[b + i];
       const gmm_stream_io& s = io[b + i];
       a[i] = frame_args(h, s.rgb, s.rgb_pitch_bytes, s.depth, s.depth_pitch_bytes, s.fg_rgb, s.fg_depth, s.fused);
-      measure = measure || a[i].wave_bytes != nullptr;
+      l.measure = l.measure || a[i].wave_bytes != nullptr;
       f[i] = next_first;
       next_first += static_cast<uint32_t>((h->npix + t.tile_pixels - 1) / t.tile_pixels);
     }
-    e = pack_descriptors(a, f, count, table + b, first + b, hs);
+    if (count == n && fits_args(a, l)) {
+      packed = false;
+      e = launch_batch_args(handles[0]->cfg.M, handles[0]->cfg.state_dtype, a, f, l, hs);
+    } else {
+      e = pack_descriptors(a, f, count, table + b, first + b, hs);
+    }
   }
-  if (e != hipSuccess) return hip_fail(e, "descriptor pack kernel launch");
-  BatchLaunch l = batch_launch(t, tuning == nullptr, static_cast<uint32_t>(total), pixels, cus);
-  l.table = table;
-  l.first = first;
-  l.n_streams = static_cast<uint32_t>(n);
-  l.measure = measure;
-  l.stream = streams_rows(hot);
-  e = launch_batch(handles[0]->cfg.M, handles[0]->cfg.state_dtype, l, hs);
+  if (e == hipSuccess && packed) e = launch_batch(handles[0]->cfg.M, handles[0]->cfg.state_dtype, l, hs);
   if (e != hipSuccess) return hip_fail(e, "static batch kernel launch");
   for (int32_t i = 0; i < n; ++i) handles[i]->last_stream = hs;
   return GMM_OK;
