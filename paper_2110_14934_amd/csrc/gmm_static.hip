@@ -30,29 +30,27 @@ static_assert(kTableBytes % 256 == 0, "the first-tile array starts 256-byte alig
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 // The batched kernel on descriptors in its own arguments: one launch instead of two where they fit,
-// which saves the pack kernel and the gap behind it. 256 threads a block, no byte counting.
+// which saves the pack kernel and the gap behind it. 256 threads a block, one block per piece, no
+// byte counting.
 template <int M, typename S, int CP>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(M <= 3 ? 6 : 5))) batch_args_kernel(
-    PackArgs p, uint32_t n_pieces, uint32_t tile_px, uint32_t piece_shift) {
+    PackArgs p, uint32_t tile_px, uint32_t piece_shift) {
   __shared__ uint32_t lds[kWavesPerBlock][48];
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = threadIdx.x / kWave;
-  const uint32_t piece_px = tile_px >> piece_shift, part_mask = (1u << piece_shift) - 1u;
-  for (uint32_t b = blockIdx.x; b < n_pieces; b += gridDim.x) {
-    const uint32_t t = b >> piece_shift;
-    const uint32_t s = find_stream(p.first, p.count, t);
-    const FrameArgs a = unpack_entry(p, s);
-    const uint32_t t0 = (t - p.first[s]) * tile_px + (b & part_mask) * piece_px;
-    process_tile<M, S, kBlock, CP, false>(a, t0, piece_px, lane, lds[wv]);
-  }
+  const uint32_t b = blockIdx.x, t = b >> piece_shift, piece_px = tile_px >> piece_shift;
+  const uint32_t s = find_stream(p.first, p.count, t);
+  const FrameArgs a = unpack_entry(p, s);
+  const uint32_t t0 = (t - p.first[s]) * tile_px + (b & ((1u << piece_shift) - 1u)) * piece_px;
+  process_tile<M, S, kBlock, CP, false>(a, t0, piece_px, lane, lds[wv]);
 }
 
 template <int M, typename S>
 static hipError_t launch_args_ms(const PackArgs& p, const BatchLaunch& l, hipStream_t s) {
   if (l.stream)
-    batch_args_kernel<M, S, kStream><<<dim3(l.grid), dim3(kBlock), 0, s>>>(p, l.n_pieces, l.tile_px, l.piece_shift);
+    batch_args_kernel<M, S, kStream><<<dim3(l.grid), dim3(kBlock), 0, s>>>(p, l.tile_px, l.piece_shift);
   else
-    batch_args_kernel<M, S, kCached><<<dim3(l.grid), dim3(kBlock), 0, s>>>(p, l.n_pieces, l.tile_px, l.piece_shift);
+    batch_args_kernel<M, S, kCached><<<dim3(l.grid), dim3(kBlock), 0, s>>>(p, l.tile_px, l.piece_shift);
   return hipGetLastError();
 }
 
@@ -69,7 +67,9 @@ static hipError_t launch_args_s(int M, const PackArgs& p, const BatchLaunch& l, 
 }
 
 bool fits_args(const FrameArgs* a, const BatchLaunch& l) {
-  if (l.n_streams > static_cast<uint32_t>(kPackPerLaunch) || l.measure || l.block != kBlock) return false;
+  if (l.n_streams > static_cast<uint32_t>(kPackPerLaunch) || l.measure || l.block != kBlock ||
+      l.grid != l.n_pieces)
+    return false;
   for (uint32_t i = 1; i < l.n_streams; ++i)
     if (!same_consts(a[0], a[i])) return false;
   return true;
