@@ -15,10 +15,12 @@ namespace rgbd {
 // 192 interleaved bytes are fetched as 48 dwords (lanes 48-63 repeat the last one), staged in
 // the wave's LDS slice and de-interleaved from there; otherwise each lane reads its own three
 // bytes. `p` must be inside the frame.
-// Frames keep the default cache policy also where rows stream: neighbouring waves share lines of the
-// colour frame (192 bytes each, lines of 128), and marked non-temporal they are fetched twice (32 VGA
-// fp16 streams 135.4 -> 132.9 us; a 16-stream tick that reads frames over the link 552 -> 542 us; 64
-// uneven fp32 streams 305 us either way).
+// NT marks the frame loads non-temporal, as the rows of streaming kernels are in fp32 state: 64 uneven
+// streams, several such batches in turn, 303.5 us a launch and 310.5 without. In 16-bit state, whose
+// rows are half as many bytes, and of frames read over the link it costs more than it keeps in the
+// caches: neighbouring waves share lines of the colour frame (192 bytes each, lines of 128), which
+// are then fetched twice (32 VGA fp16 streams 135.4 us, 132.9 without; a 16-stream fp16 tick 552 and
+// 542 us).
 struct RgbLoad {
   bool staged;
   uint32_t w;           // staged: this lane's dword of the wave's bytes
@@ -30,13 +32,14 @@ struct RgbLoad {
 // bytes, with no row arithmetic and no per-stream test.
 constexpr int kFramesDense = 16;
 
-template <bool DENSE = false>
+template <bool NT = false, bool DENSE = false>
 __device__ __forceinline__ RgbLoad issue_rgb_pixel(const FrameArgs& a, uint32_t p, uint32_t wave_base, int lane) {
   RgbLoad r{};
   r.staged = (DENSE || a.rgb_dense) && (wave_base + kWave <= a.npix);
   if (r.staged) {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(a.rgb + 3 * static_cast<uint64_t>(wave_base));
-    r.w = src[lane < 48 ? lane : 47];
+    if constexpr (NT) r.w = __builtin_nontemporal_load(&src[lane < 48 ? lane : 47]);
+    else r.w = src[lane < 48 ? lane : 47];
   } else {
     const uint8_t* b;
     if constexpr (DENSE) {
@@ -69,9 +72,12 @@ __device__ __forceinline__ void finish_rgb_pixel(const RgbLoad& r, int lane, uin
   }
 }
 
-template <bool DENSE = false>
+template <bool NT = false, bool DENSE = false>
 __device__ __forceinline__ float load_depth_pixel(const FrameArgs& a, uint32_t p) {
-  if (DENSE || a.depth_dense) return static_cast<float>(a.depth[p]);
+  if (DENSE || a.depth_dense) {
+    if constexpr (NT) return static_cast<float>(__builtin_nontemporal_load(&a.depth[p]));
+    else return static_cast<float>(a.depth[p]);
+  }
   const uint32_t y = p / static_cast<uint32_t>(a.width);
   const uint32_t xx = p - y * static_cast<uint32_t>(a.width);
   const uint16_t* row = reinterpret_cast<const uint16_t*>(
@@ -290,10 +296,10 @@ __device__ __forceinline__ void process_pixel(const FrameArgs& a, uint32_t p, in
   // count down in issue order, so the wait for the colour bytes, which the LDS staging needs at
   // once, covers only them while the state prefixes stay in flight.
   const uint32_t pc = valid ? p : a.npix - 1;
-  constexpr bool dense = (MODE & kFramesDense) != 0;
+  constexpr bool dense = (MODE & kFramesDense) != 0, nt = CP == kStream && kScaled<S>;
   RgbLoad rl{};
-  if (do_c) rl = issue_rgb_pixel<dense>(a, pc, wave_base, lane);
-  const float xd = do_d ? load_depth_pixel<dense>(a, pc) : 0.f;
+  if (do_c) rl = issue_rgb_pixel<nt, dense>(a, pc, wave_base, lane);
+  const float xd = do_d ? load_depth_pixel<nt, dense>(a, pc) : 0.f;
   // the flags byte: List 1 state (bits 0-3) and, in the scaled form, the depth hole count
   constexpr bool do_flags = do_f || (kScaled<S> && do_d);
   const uint32_t fst = do_flags ? a.fstate[pc] : 0u;
