@@ -42,8 +42,8 @@ PROFILE_TRAFFIC = {
 KERNEL_SOURCES = {
     "frame": ("csrc/gmm_device.hpp", "csrc/gmm_frame.hpp", "csrc/gmm_internal.hpp", "csrc/gmm_kernels.hip",
               "build.py"),
-    "batch": ("csrc/gmm_device.hpp", "csrc/gmm_frame.hpp", "csrc/gmm_internal.hpp", "csrc/gmm_batch.hip",
-              "build.py"),
+    "batch": ("csrc/gmm_device.hpp", "csrc/gmm_frame.hpp", "csrc/gmm_internal.hpp", "csrc/gmm_batch.hpp",
+              "csrc/gmm_batch.hip", "build.py"),
 }
 FRAME_KERNEL_SOURCES = KERNEL_SOURCES["frame"]
 MAX_POOL = 16   # host worker processes of the oracle leg (the GPU machine's CPU share for one GPU)

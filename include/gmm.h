@@ -202,7 +202,9 @@ gmm_status gmm_state_size(const gmm_handle* h, size_t* n_doubles);
  * weights (a frame's common decay of every weight goes into the scale alone); a depth pixel
  * that kept its state through k missing readings carries the factor (1/(1-alpha))^k besides.
  * The canonical weight is the fp32 product of scale and factor (as the kernels form it) times
- * the scaled weight, exact in float64. Every other value is copied exactly.
+ * the scaled weight, exact in float64. Every other value is copied exactly. The values are
+ * converted on the device through one 8 MB buffer of the library per device: reads and writes of
+ * states on one device wait for each other.
  */
 gmm_status gmm_read_state(gmm_handle* h, double* host_out, void* stream);
 

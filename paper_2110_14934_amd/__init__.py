@@ -110,7 +110,7 @@ class Segmenter:
 
 
 class Batch:
-    """A set of Segmenters advanced together by one persistent launch per frame-set."""
+    """A set of Segmenters advanced together by one launch per frame-set."""
 
     def __init__(self, segmenters, n_slots: int = 1):
         self.segs = list(segmenters)
