@@ -177,26 +177,27 @@ static void destroy_exec(gmm_exec* x) {
 }
 
 // The device address of `bytes` of host memory at p that the kernels of `device` can use in place:
-// page-locked there, coherent, from one allocation and aligned to `align`. NULL if it is not. Asked
-// anew for every buffer of every tick: memory at an address can change between ticks.
+// page-locked there, coherent, all of it in one allocation and aligned to `align`. NULL if it is not.
+// The allocation's extent is asked for: that both ends of a buffer are page-locked says nothing about
+// what lies between them. Asked anew for every buffer of every tick: memory at an address can change
+// between ticks.
 static void* in_place(const void* p, size_t bytes, size_t align, int device) {
   if (!p || reinterpret_cast<uintptr_t>(p) % align) return nullptr;
-  void* first = nullptr;
-  for (int end = 0; end < 2; ++end) {
-    hipPointerAttribute_t a{};
-    const char* q = static_cast<const char*>(p) + (end ? bytes - 1 : 0);
-    if (hipPointerGetAttributes(&a, q) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
+  hipPointerAttribute_t a{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  hipError_t e = hipPointerGetAttributes(&a, p);
+  if (e == hipSuccess) {
     if (a.type != hipMemoryTypeHost || a.device != device || !a.devicePointer || (a.allocationFlags & hipHostMallocNonCoherent))
       return nullptr;
-    if (!end)
-      first = a.devicePointer;
-    else if (static_cast<char*>(a.devicePointer) != static_cast<char*>(first) + (bytes - 1))
-      return nullptr;
+    e = hipMemGetAddressRange(&base, &size, a.devicePointer);
   }
-  return first;
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  const size_t at = static_cast<size_t>(static_cast<char*>(a.devicePointer) - static_cast<char*>(base));
+  return at <= size && bytes <= size - at ? a.devicePointer : nullptr;
 }
 
 static size_t mask_bytes(const gmm_handle* h) { return static_cast<size_t>((h->npix + 63) / 64) * 8; }

@@ -1,0 +1,249 @@
+// What the library asks of the HIP runtime, without a GPU: the program stands in for the runtime
+// (its symbols come before libamdhip64's), remembers allocations, copies and launches, and runs no
+// kernel. Each check drives the C ABI and looks at the launches and copies that a call made.
+//
+//   routes_check NAME...
+#include <cxxabi.h>
+#include <hip/hip_runtime_api.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <mutex>
+#include <string>
+#include <vector>
+
+#include "gmm.h"
+
+// ---- the stand-in runtime ----------------------------------------------------------------------
+
+struct Region {
+  size_t bytes;
+  hipMemoryType type;
+  unsigned flags;
+};
+struct Launch {
+  std::string name;
+  unsigned grid, block;
+  size_t lds;
+};
+
+struct Runtime {
+  std::mutex mu;
+  std::map<const void*, std::string> kernels;
+  std::map<uintptr_t, Region> regions;
+  std::vector<Launch> launches;
+  size_t h2d = 0, d2h = 0;  // asynchronous copies
+};
+static Runtime& rt() {
+  static Runtime r;
+  return r;
+}
+
+static std::map<uintptr_t, Region>::iterator region_of(const void* p) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+  auto it = rt().regions.upper_bound(a);
+  if (it == rt().regions.begin()) return rt().regions.end();
+  --it;
+  return a < it->first + it->second.bytes ? it : rt().regions.end();
+}
+
+static hipError_t allocate(void** p, size_t n, hipMemoryType type, unsigned flags) {
+  *p = std::aligned_alloc(4096, (n + 4095) / 4096 * 4096);
+  if (!*p) return hipErrorOutOfMemory;
+  std::lock_guard<std::mutex> lk(rt().mu);
+  rt().regions[reinterpret_cast<uintptr_t>(*p)] = Region{n, type, flags};
+  return hipSuccess;
+}
+
+static hipError_t release(void* p) {
+  {
+    std::lock_guard<std::mutex> lk(rt().mu);
+    rt().regions.erase(reinterpret_cast<uintptr_t>(p));
+  }
+  std::free(p);
+  return hipSuccess;
+}
+
+extern "C" {
+
+void** __hipRegisterFatBinary(const void*) {
+  static void* module;
+  return &module;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
+  int st = 0;
+  char* d = abi::__cxa_demangle(name, nullptr, nullptr, &st);
+  rt().kernels[host] = st == 0 ? d : name;
+  std::free(d);
+}
+void __hipRegisterVar(void**, void* var, char*, char*, int, size_t n, int, int) {
+  rt().regions[reinterpret_cast<uintptr_t>(var)] = Region{n, hipMemoryTypeDevice, 0};
+}
+
+static thread_local struct {
+  dim3 grid, block;
+  size_t lds;
+  hipStream_t s;
+} g_call;
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t s) {
+  g_call = {g, b, lds, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t* s) {
+  *g = g_call.grid;
+  *b = g_call.block;
+  *lds = g_call.lds;
+  *s = g_call.s;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void**, size_t lds, hipStream_t) {
+  std::lock_guard<std::mutex> lk(rt().mu);
+  rt().launches.push_back(Launch{rt().kernels[f], g.x, b.x, lds});
+  return hipSuccess;
+}
+
+hipError_t hipGetDeviceCount(int* n) { return *n = 1, hipSuccess; }
+hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "stand-in error"; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
+hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) {
+  std::memset(p, 0, sizeof *p);
+  std::strcpy(p->gcnArchName, "gfx950");
+  p->multiProcessorCount = 256;
+  return hipSuccess;
+}
+hipError_t hipGetSymbolAddress(void** p, const void* sym) { return *p = const_cast<void*>(sym), hipSuccess; }
+
+hipError_t hipMalloc(void** p, size_t n) { return allocate(p, n, hipMemoryTypeDevice, 0); }
+hipError_t hipFree(void* p) { return release(p); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) { return allocate(p, n, hipMemoryTypeHost, flags); }
+hipError_t hipHostFree(void* p) { return release(p); }
+hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind kind, hipStream_t) {
+  std::lock_guard<std::mutex> lk(rt().mu);
+  (kind == hipMemcpyHostToDevice ? rt().h2d : rt().d2h) += kind == hipMemcpyDeviceToDevice ? 0 : 1;
+  return hipSuccess;
+}
+
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+  std::lock_guard<std::mutex> lk(rt().mu);
+  std::memset(a, 0, sizeof *a);
+  const auto it = region_of(p);
+  a->type = it == rt().regions.end() ? hipMemoryTypeUnregistered : it->second.type;
+  a->device = it == rt().regions.end() ? -2 : 0;
+  if (it == rt().regions.end()) return hipSuccess;
+  a->devicePointer = const_cast<void*>(p);
+  a->hostPointer = it->second.type == hipMemoryTypeHost ? a->devicePointer : nullptr;
+  a->allocationFlags = it->second.flags;
+  return hipSuccess;
+}
+hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* n, hipDeviceptr_t p) {
+  std::lock_guard<std::mutex> lk(rt().mu);
+  const auto it = region_of(p);
+  if (it == rt().regions.end()) return hipErrorNotFound;
+  *base = reinterpret_cast<hipDeviceptr_t>(it->first);
+  *n = it->second.bytes;
+  return hipSuccess;
+}
+
+hipError_t hipEventCreate(hipEvent_t* e) { return *e = reinterpret_cast<hipEvent_t>(1), hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.f, hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return *s = reinterpret_cast<hipStream_t>(1), hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+
+}  // extern "C"
+
+// ---- what the checks share ---------------------------------------------------------------------
+
+static int g_bad = 0;
+#define EXPECT(cond)                                                   \
+  do {                                                                 \
+    if (!(cond)) std::printf("line %d: %s\n", __LINE__, #cond), ++g_bad; \
+  } while (0)
+#define OK(call) EXPECT((call) == GMM_OK)
+
+static gmm_handle* handle(int w, int h, int modalities = GMM_RGB | GMM_DEPTH, int M = 5, int dtype = GMM_F32) {
+  gmm_config c;
+  OK(gmm_config_default(&c, w, h, modalities, M));
+  c.state_dtype = dtype;
+  gmm_handle* g = nullptr;
+  OK(gmm_create(&c, &g));
+  return g;
+}
+
+// Page-locked host memory.
+static uint8_t* pinned(size_t n, unsigned flags = 0) {
+  void* p = nullptr;
+  (void)hipHostMalloc(&p, n, flags);
+  return static_cast<uint8_t*>(p);
+}
+
+struct Counts {
+  size_t h2d, d2h;
+};
+
+// One tick of an executor, waited for: the copies of frames and masks it made.
+static Counts tick(gmm_exec* x, const std::vector<gmm_exec_item>& items) {
+  const Counts before{rt().h2d, rt().d2h};
+  OK(gmm_exec_launch(x, items.data(), static_cast<int32_t>(items.size()), nullptr));
+  OK(gmm_exec_drain(x));
+  return Counts{rt().h2d - before.h2d, rt().d2h - before.d2h};
+}
+
+// ---- checks ------------------------------------------------------------------------------------
+
+// A frame is used in place only if all of it lies in one page-locked allocation: its ends may lie in
+// two with memory between them that the GPU cannot read.
+static void gap() {
+  constexpr int W = 320, H = 240;
+  constexpr size_t n = size_t(W) * H * 3;
+  gmm_exec* x = nullptr;
+  OK(gmm_exec_create(0, 2, &x));
+  gmm_handle* h = handle(W, H, GMM_RGB);
+  OK(gmm_exec_attach(x, h, nullptr));
+  uint8_t* whole = pinned(n + 8192);
+  uint64_t* mask = reinterpret_cast<uint64_t*>(pinned(W * H / 8));
+  std::vector<gmm_exec_item> it{{h, whole, nullptr, mask, nullptr, nullptr}};
+  EXPECT(tick(x, it).h2d == 0);
+  // the same memory as two page-locked regions with an ordinary page between them
+  rt().regions.erase(reinterpret_cast<uintptr_t>(whole));
+  rt().regions[reinterpret_cast<uintptr_t>(whole)] = Region{4096, hipMemoryTypeHost, 0};
+  rt().regions[reinterpret_cast<uintptr_t>(whole) + 8192] = Region{n, hipMemoryTypeHost, 0};
+  EXPECT(tick(x, it).h2d == 1);
+  it[0].host_rgb = whole + 8192;  // inside the second region
+  EXPECT(tick(x, it).h2d == 0);
+  it[0].host_rgb = whole + 8196;  // its last bytes past the region's end
+  EXPECT(tick(x, it).h2d == 1);
+  // a mask with such a gap goes through the device arena
+  it[0].host_rgb = whole + 8192;
+  it[0].host_fg_rgb = reinterpret_cast<uint64_t*>(whole);
+  EXPECT(tick(x, it).d2h == 1);
+  OK(gmm_exec_destroy(x));
+  OK(gmm_destroy(h));
+}
+
+int main(int argc, char** argv) {
+  const std::map<std::string, std::function<void()>> checks = {
+      {"gap", gap},
+  };
+  for (int i = 1; i < argc; ++i) {
+    const auto it = checks.find(argv[i]);
+    if (it == checks.end()) return std::printf("no check %s\n", argv[i]), 2;
+    it->second();
+  }
+  std::printf(g_bad ? "%d failed\n" : "routes ok\n", g_bad);
+  return g_bad ? 1 : 0;
+}
