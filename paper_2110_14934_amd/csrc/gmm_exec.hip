@@ -176,8 +176,17 @@ static void destroy_exec(gmm_exec* x) {
   delete x;
 }
 
+static bool coherent(unsigned flags) {
+  constexpr unsigned kHarmless = hipHostMallocCoherent | hipHostMallocPortable | hipHostMallocMapped;
+  return flags == hipHostMallocDefault || ((flags & hipHostMallocCoherent) && !(flags & ~kHarmless));
+}
+
 // The device address of `bytes` of host memory at p that the kernels of `device` can use in place:
 // page-locked there, coherent, all of it in one allocation and aligned to `align`. NULL if it is not.
+// Coherent is what was allocated (or registered) with no flags, the page-locked default, or as
+// hipHostMallocCoherent: frames rewritten between ticks must not be read from a cache, and masks must
+// be in host memory when the tick's event is done. Flags that leave it open, and registrations as
+// coarse-grained or read-only memory, are not taken.
 // The allocation's extent is asked for: that both ends of a buffer are page-locked says nothing about
 // what lies between them. Asked anew for every buffer of every tick: memory at an address can change
 // between ticks.
@@ -188,8 +197,7 @@ static void* in_place(const void* p, size_t bytes, size_t align, int device) {
   size_t size = 0;
   hipError_t e = hipPointerGetAttributes(&a, p);
   if (e == hipSuccess) {
-    if (a.type != hipMemoryTypeHost || a.device != device || !a.devicePointer || (a.allocationFlags & hipHostMallocNonCoherent))
-      return nullptr;
+    if (a.type != hipMemoryTypeHost || a.device != device || !a.devicePointer || !coherent(a.allocationFlags)) return nullptr;
     e = hipMemGetAddressRange(&base, &size, a.devicePointer);
   }
   if (e != hipSuccess) {

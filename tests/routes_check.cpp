@@ -235,9 +235,45 @@ static void gap() {
   OK(gmm_destroy(h));
 }
 
+// Only memory known to be coherent between host and device is used in place; every other kind of
+// page-locked memory is copied.
+static void coherence() {
+  constexpr int W = 64, H = 64;
+  constexpr size_t n = size_t(W) * H * 3;
+  gmm_exec* x = nullptr;
+  OK(gmm_exec_create(0, 2, &x));
+  gmm_handle* h = handle(W, H, GMM_RGB);
+  OK(gmm_exec_attach(x, h, nullptr));
+  const struct {
+    unsigned flags;
+    bool in_place;
+  } kinds[] = {
+      {hipHostMallocDefault, true},
+      {hipHostMallocCoherent, true},
+      {hipHostMallocCoherent | hipHostMallocPortable, true},
+      {hipHostMallocCoherent | hipHostMallocMapped, true},
+      {hipHostMallocNonCoherent, false},
+      {hipHostMallocPortable, false},
+      {hipHostMallocMapped, false},
+      {hipHostMallocWriteCombined, false},
+      {hipExtHostRegisterCoarseGrained, false},  // also hipHostRegisterReadOnly, which a mask must not be written to
+      {hipHostMallocCoherent | hipExtHostRegisterCoarseGrained, false},
+  };
+  for (const auto& k : kinds) {
+    uint8_t* frame = pinned(n, k.flags);
+    uint64_t* mask = reinterpret_cast<uint64_t*>(pinned(W * H / 8, k.flags));
+    const Counts c = tick(x, {{h, frame, nullptr, mask, nullptr, nullptr}});
+    if (c.h2d != (k.in_place ? 0u : 1u) || c.d2h != (k.in_place ? 0u : 1u))
+      std::printf("flags %#x: %zu frames and %zu masks copied\n", k.flags, c.h2d, c.d2h), ++g_bad;
+  }
+  OK(gmm_exec_destroy(x));
+  OK(gmm_destroy(h));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
+      {"coherence", coherence},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);
