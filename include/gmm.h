@@ -336,8 +336,10 @@ typedef struct gmm_exec gmm_exec;
 /* One stream's frame in a tick. Frames are read from host memory with dense rows (pitch
  * 3*width for colour, 2*width for depth); masks are written to host memory. Host buffers should be
  * page-locked (hipHostMalloc, pinned torch tensors): colour frames aligned to 4 bytes, depth frames
- * to 2 and masks to 8 in coherent page-locked memory are read and written by the kernel in place;
- * any others are copied by DMA, and only page-locked copies overlap device work. All must stay
+ * to 2 and masks to 8 in coherent page-locked memory (hipHostMalloc's default, or
+ * hipHostMallocCoherent), each within one allocation, are read and written by the kernel in place;
+ * any others are copied by DMA, and only page-locked copies overlap device work. A mask may lie over
+ * a frame or another mask of its tick: masks are then copied back after the kernel, in item order. All must stay
  * valid and untouched until the tick completes (gmm_exec_poll). A NULL mask pointer skips that
  * mask; non-NULL host_fused runs List 1 for the stream (two-modality streams only). */
 typedef struct {

@@ -21,6 +21,7 @@
 #include <condition_variable>
 #include <cstring>
 #include <deque>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <new>
@@ -208,6 +209,26 @@ static void* in_place(const void* p, size_t bytes, size_t align, int device) {
   return at <= size && bytes <= size - at ? a.devicePointer : nullptr;
 }
 
+// Host memory of a tick: a frame that the kernel reads in place, or a mask.
+struct Buffer {
+  const void *begin, *end;
+  bool mask;
+};
+
+// Whether every mask is apart from every other mask and from the frames read in place (frames may
+// share memory). Reorders `b`.
+static bool masks_apart(std::vector<Buffer>& b) {
+  const std::less<const void*> before;
+  std::sort(b.begin(), b.end(), [&](const Buffer& x, const Buffer& y) { return before(x.begin, y.begin); });
+  const void *end = nullptr, *mask_end = nullptr;  // of the buffers and of the masks so far
+  for (const Buffer& x : b) {
+    if (before(x.begin, x.mask ? end : mask_end)) return false;
+    if (before(end, x.end)) end = x.end;
+    if (x.mask && before(mask_end, x.end)) mask_end = x.end;
+  }
+  return true;
+}
+
 static size_t mask_bytes(const gmm_handle* h) { return static_cast<size_t>((h->npix + 63) / 64) * 8; }
 
 extern "C" {
@@ -385,6 +406,8 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     size_t off[3];       // offset in the arena, or SIZE_MAX
   };
   std::vector<Place> place(n);
+  std::vector<Buffer> used;
+  used.reserve(5 * static_cast<size_t>(n));
   size_t mask_total = 0;
   bool linked = false;  // some frame is read in place
   for (int32_t i = 0; i < n; ++i) {
@@ -395,10 +418,25 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     p.rgb = static_cast<const uint8_t*>(in_place(it.host_rgb, px * 3, 4, x->device));
     p.depth = static_cast<const uint16_t*>(in_place(it.host_depth, px * 2, 2, x->device));
     linked = linked || p.rgb || p.depth;
+    if (p.rgb) used.push_back({it.host_rgb, it.host_rgb + px * 3, false});
+    if (p.depth) used.push_back({it.host_depth, it.host_depth + px, false});
     void* want[3] = {it.host_fg_rgb, it.host_fg_depth, it.host_fused};
-    const bool write[3] = {has_rgb(h), has_depth(h), it.host_fused != nullptr};
     for (int m = 0; m < 3; ++m) {
       p.mask[m] = static_cast<uint64_t*>(in_place(want[m], mb, 8, x->device));
+      if (want[m]) used.push_back({want[m], static_cast<char*>(want[m]) + mb, true});
+    }
+  }
+  // A mask over memory that the kernel reads, or over another mask, comes from the arena after the
+  // kernel, and with it all masks of the tick, in the order of the items.
+  const bool apart = masks_apart(used);
+  for (int32_t i = 0; i < n; ++i) {
+    const gmm_exec_item& it = items[i];
+    const gmm_handle* h = it.handle;
+    const size_t mb = mask_bytes(h);
+    Place& p = place[i];
+    const bool write[3] = {has_rgb(h), has_depth(h), it.host_fused != nullptr};
+    for (int m = 0; m < 3; ++m) {
+      if (!apart) p.mask[m] = nullptr;
       p.off[m] = SIZE_MAX;
       if (write[m] && !p.mask[m]) {
         p.off[m] = mask_total;

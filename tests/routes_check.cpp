@@ -270,10 +270,50 @@ static void coherence() {
   OK(gmm_destroy(h));
 }
 
+// Masks that share memory with a frame or another mask of the tick are delivered after the kernel, in
+// the order of the items, as if every frame had been copied in first: they are not written in place.
+static void overlap() {
+  constexpr int W = 64, H = 64;
+  constexpr size_t px = size_t(W) * H, words = px / 64;
+  gmm_exec* x = nullptr;
+  OK(gmm_exec_create(0, 2, &x));
+  gmm_handle* h[2] = {handle(W, H), handle(W, H)};
+  for (auto* g : h) OK(gmm_exec_attach(x, g, nullptr));
+  uint8_t* rgb[2] = {pinned(px * 3), pinned(px * 3)};
+  uint16_t* depth[2] = {reinterpret_cast<uint16_t*>(pinned(px * 2)), reinterpret_cast<uint16_t*>(pinned(px * 2))};
+  uint64_t* m = reinterpret_cast<uint64_t*>(pinned(6 * words * 8));
+  const std::vector<gmm_exec_item> apart{{h[0], rgb[0], depth[0], m, m + words, m + 2 * words},
+                                         {h[1], rgb[1], depth[1], m + 3 * words, m + 4 * words, m + 5 * words}};
+  EXPECT(tick(x, apart).d2h == 0);
+  std::vector<gmm_exec_item> it = apart;
+  it[0].host_fg_rgb = reinterpret_cast<uint64_t*>(rgb[0]);  // over its own colour frame
+  EXPECT(tick(x, it).d2h == 1);
+  it = apart;
+  it[0].host_fused = reinterpret_cast<uint64_t*>(depth[1]) + 3;  // inside another stream's depth frame
+  EXPECT(tick(x, it).d2h == 1);
+  it = apart;
+  it[1].host_fg_depth = it[1].host_fg_rgb;  // one buffer for two masks
+  EXPECT(tick(x, it).d2h == 1);
+  it = apart;
+  it[1].host_fused = m + words - 1;  // across the end of one mask and the start of the next
+  EXPECT(tick(x, it).d2h == 1);
+  it = apart;
+  it[1].host_rgb = rgb[0];  // frames may share memory: nothing writes them
+  it[1].host_depth = reinterpret_cast<uint16_t*>(rgb[0] + 2);
+  EXPECT(tick(x, it).d2h == 0);
+  it[1].host_depth = depth[1];
+  it[0].host_fg_rgb = reinterpret_cast<uint64_t*>(rgb[0] + 8);  // a mask in a frame that two streams share
+  EXPECT(tick(x, it).d2h == 1);
+  EXPECT(tick(x, apart).d2h == 0);
+  OK(gmm_exec_destroy(x));
+  for (auto* g : h) OK(gmm_destroy(g));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
       {"coherence", coherence},
+      {"overlap", overlap},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);

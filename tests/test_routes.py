@@ -27,7 +27,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["gap", "coherence"])
+@pytest.mark.parametrize("check", ["gap", "coherence", "overlap"])
 def test_routes(exe, check):
     # freed memory is overwritten, so that a read of it shows
     r = subprocess.run([exe, check], capture_output=True, text=True, timeout=60,
