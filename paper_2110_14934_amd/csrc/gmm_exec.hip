@@ -55,6 +55,7 @@ struct Attached {
   uint8_t* d_rgb[kFramesInFlight] = {};        // dense colour slots (3 bytes per pixel)
   uint16_t* d_depth[kFramesInFlight] = {};     // dense depth slots (2 bytes per pixel)
   size_t bytes = 0;
+  size_t hot = 0;                              // hot_bytes of the stream
   int in_flight = 0;
   uint64_t frames = 0;                         // frames launched; frame f uses slot f % 2
 };
@@ -310,8 +311,9 @@ gmm_status gmm_exec_attach(gmm_exec* x, gmm_handle* h, size_t* device_bytes) {
   a.base = mem;
   place_slots(a, h, static_cast<uint8_t*>(mem));
   a.bytes = slots;
+  a.hot = hot_bytes(h);
   x->attached[h] = a;
-  x->hot += hot_bytes(h);
+  x->hot += a.hot;
   x->M = h->cfg.M;
   x->dtype = h->cfg.state_dtype;
   if (device_bytes) *device_bytes = a.bytes;
@@ -325,8 +327,8 @@ gmm_status gmm_exec_detach(gmm_exec* x, gmm_handle* h) {
   if (it == x->attached.end()) return fail(GMM_ERR_INVALID_ARG, "handle not attached");
   x->cv.wait(lk, [&] { return it->second.in_flight == 0; });  // its last frame has completed
   void* base = it->second.base;
+  x->hot -= it->second.hot;
   x->attached.erase(it);
-  x->hot -= hot_bytes(h);
   lk.unlock();
   DeviceGuard g(x->device);
   if (base) (void)hipFree(base);
@@ -607,8 +609,9 @@ gmm_status gmm_exec_create_stream(gmm_exec* x, const gmm_config* cfg, void* mem,
     return hip_fail(e, "state initialisation");
   }
   h->last_stream = x->s_compute;
+  a.hot = hot_bytes(h);
   x->attached[h] = a;
-  x->hot += hot_bytes(h);
+  x->hot += a.hot;
   x->M = h->cfg.M;
   x->dtype = h->cfg.state_dtype;
   *out = h;
@@ -622,8 +625,8 @@ gmm_status gmm_exec_destroy_stream(gmm_exec* x, gmm_handle* h) {
   auto it = x->attached.find(h);
   if (it == x->attached.end()) return fail(GMM_ERR_INVALID_ARG, "handle not attached");
   x->cv.wait(lk, [&] { return it->second.in_flight == 0; });  // its last frame has completed
+  x->hot -= it->second.hot;
   x->attached.erase(it);
-  x->hot -= hot_bytes(h);
   lk.unlock();
   delete h;
   return GMM_OK;

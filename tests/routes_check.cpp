@@ -309,11 +309,47 @@ static void overlap() {
   for (auto* g : h) OK(gmm_destroy(g));
 }
 
+// The policy (CP) of the last batched launch: 0 rows kept in the caches, 2 rows streamed.
+static int policy() {
+  for (size_t i = rt().launches.size(); i-- > 0;) {
+    const std::string k = rt().launches[i].name.substr(0, rt().launches[i].name.find('('));
+    const size_t last = k.rfind(',');
+    if (k.find("batch_args_kernel<") != std::string::npos) return std::atoi(k.c_str() + last + 1);  // <M, S, CP>
+    if (k.find("batch_kernel<") != std::string::npos)  // <M, S, BLOCK, CP, MEASURE>
+      return std::atoi(k.c_str() + k.rfind(',', last - 1) + 1);
+  }
+  return -1;
+}
+
+// A stream may be detached after its handle has gone: the handle is a key then, its memory is not
+// read, and the executor's other streams are served as if it had never been there.
+static void detach() {
+  constexpr int W = 64, H = 64;
+  gmm_exec* x = nullptr;
+  OK(gmm_exec_create(0, 2, &x));
+  gmm_handle *gone = handle(W, H, GMM_RGB), *h = handle(W, H, GMM_RGB);
+  OK(gmm_exec_attach(x, h, nullptr));
+  OK(gmm_exec_attach(x, gone, nullptr));
+  OK(gmm_destroy(gone));
+  gmm_handle* other = handle(1024, 1024, GMM_RGB);  // most likely in the memory of the first
+  const size_t before = rt().regions.size();
+  OK(gmm_exec_detach(x, gone));
+  EXPECT(rt().regions.size() == before - 1);  // its frame slots
+  EXPECT(gmm_exec_detach(x, gone) == GMM_ERR_INVALID_ARG);
+  uint8_t* frame = pinned(W * H * 3);
+  (void)tick(x, {{h, frame, nullptr, reinterpret_cast<uint64_t*>(pinned(W * H / 8)), nullptr, nullptr}});
+  EXPECT(policy() == 0);  // one small stream stays in the caches
+  OK(gmm_exec_destroy(x));
+  OK(gmm_destroy(h));
+  OK(gmm_destroy(other));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
       {"coherence", coherence},
       {"overlap", overlap},
+      {"detach", detach},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);
