@@ -246,8 +246,8 @@ typedef struct {
 /* Launch shape of the batched kernel: threads per block (256 or 512), pixels per tile (a multiple
  * of block_threads, at most 64x it; a tile never spans two streams) and blocks per compute unit
  * (1..32): grid = blocks_per_cu x CU count, capped at the tile count, each block walking tiles;
- * where blocks_per_cu x block_threads is 2048 or more, all a CU holds, one block per tile. A
- * launch with the default shape, none having been set or found, may cut tiles into smaller pieces. */
+ * where blocks_per_cu x block_threads is 2048 or more, all a CU holds, one block per tile. The
+ * default shape, {256, 1024, 8}, leaves it to the library, which may cut tiles into smaller pieces. */
 typedef struct {
   int32_t block_threads;
   int32_t tile_pixels;

@@ -97,7 +97,7 @@ hipError_t launch_batch(int M, int dtype, const BatchLaunch& l, hipStream_t s) {
 // the dispatcher then hands the next piece to whichever CU is free, where blocks walking fixed
 // pieces wait for the slowest (64 uneven fp32 streams, M = 5: 360 us walking 1024-pixel tiles with 8 blocks per
 // CU, 315 us one block per tile). Fewer blocks per CU walk.
-// Pieces: a launch whose shape the caller left open cuts the default tiles of 1024 pixels into
+// Pieces: a launch of the default shape, which leaves it to the library (is_open), cuts the default tiles of 1024 pixels into
 // pieces of 512, or of 256 when all pixels together are few (kSmallBatchPixels): larger pieces
 // spread a block's start (the search, the descriptor) over more pixels, smaller ones leave a
 // shorter chain in each wave and an evener end. Pieces of 256 / 512 / 1024 pixels: 64 uneven fp32
@@ -107,11 +107,11 @@ hipError_t launch_batch(int M, int dtype, const BatchLaunch& l, hipStream_t s) {
 constexpr uint64_t kSmallBatchPixels = uint64_t(1) << 20;
 constexpr uint32_t kMaxGrid = 1u << 22;  // blocks, so that grid x block stays below 2^32 threads
 
-BatchLaunch batch_launch(const gmm_batch_tuning& t, bool open, uint32_t n_tiles, uint64_t pixels, int cu_count) {
+BatchLaunch batch_launch(const gmm_batch_tuning& t, uint32_t n_tiles, uint64_t pixels, int cu_count) {
   BatchLaunch l{};
   l.block = t.block_threads;
   l.tile_px = static_cast<uint32_t>(t.tile_pixels);
-  l.piece_shift = !open || n_tiles >= (1u << 28) ? 0u : (pixels < kSmallBatchPixels ? 2u : 1u);
+  l.piece_shift = !is_open(t) || n_tiles >= (1u << 28) ? 0u : (pixels < kSmallBatchPixels ? 2u : 1u);
   l.n_pieces = n_tiles << l.piece_shift;
   const bool walk = t.blocks_per_cu * t.block_threads < 2048;
   const uint32_t want = walk ? static_cast<uint32_t>(t.blocks_per_cu) * static_cast<uint32_t>(cu_count) : kMaxGrid;
@@ -196,7 +196,6 @@ struct gmm_batch {
   uint64_t pixels = 0;                       // of one frame of every stream
   size_t hot = 0;                            // hot_bytes of all streams
   gmm_batch_tuning tuning = kDefaultTuning;
-  bool shape_open = true;                    // no launch shape set or found: batch_launch may cut the tiles
   hipStream_t last_stream = nullptr;
 };
 
@@ -238,12 +237,11 @@ static gmm_status apply_tuning(gmm_batch* b, const gmm_batch_tuning& t) {
     if (st != GMM_OK) return st;
   }
   b->tuning = t;
-  b->shape_open = false;
   return GMM_OK;
 }
 
 static hipError_t run_slot(gmm_batch* b, int slot, hipStream_t s) {
-  BatchLaunch l = batch_launch(b->tuning, b->shape_open, b->n_tiles, b->pixels, b->cu_count);
+  BatchLaunch l = batch_launch(b->tuning, b->n_tiles, b->pixels, b->cu_count);
   l.table = b->d_table + static_cast<size_t>(slot) * n_streams(b);
   l.first = b->d_first_tile;
   l.n_streams = static_cast<uint32_t>(n_streams(b));

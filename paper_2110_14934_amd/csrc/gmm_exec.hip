@@ -105,7 +105,6 @@ struct gmm_exec {
   int M = -1, dtype = -1;
   int cu_count = 0;
   gmm_batch_tuning tuning = kDefaultTuning;
-  bool shape_open = true;  // no launch shape set
   hipStream_t s_in[kCopyInStreams] = {};
   hipStream_t s_compute = nullptr, s_out = nullptr;
   std::vector<Slot> slots;
@@ -290,7 +289,6 @@ gmm_status gmm_exec_set_tuning(gmm_exec* x, const gmm_batch_tuning* t) {
   if (t->blocks_per_cu < 1 || t->blocks_per_cu > 32) return fail(GMM_ERR_INVALID_ARG, "blocks_per_cu must be in 1..32");
   std::lock_guard<std::mutex> lk(x->mu);
   x->tuning = *t;
-  x->shape_open = false;
   return GMM_OK;
 }
 
@@ -370,12 +368,10 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     x->cv.wait(lk, [&] { return !s.busy; });
   }
   gmm_batch_tuning tun;
-  bool open;
   size_t hot;
   {
     std::lock_guard<std::mutex> lk(x->mu);
     tun = x->tuning;
-    open = x->shape_open;
     hot = x->hot;
   }
   // work list: n descriptors followed by n tile starts
@@ -460,10 +456,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
   // A tick that reads frames over the link always takes the default shape, one block per piece:
   // what is in flight then keeps the link busy, where fewer blocks that walk tiles do not (640
   // mixed streams a tick: 52.3 GB/s, 38.5 with 4 blocks of 256 threads per CU).
-  if (linked) {
-    tun = kDefaultTuning;
-    open = true;
-  }
+  if (linked) tun = kDefaultTuning;
   const uint32_t tile_px = static_cast<uint32_t>(tun.tile_pixels);
   s.outs.clear();
   uint32_t* h_first = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s.h_table) + tab);
@@ -516,7 +509,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     if (e == hipSuccess) e = hipStreamWaitEvent(x->s_compute, s.h2d_done[c], 0);
   }
   if (e == hipSuccess) {
-    BatchLaunch l = batch_launch(tun, open, static_cast<uint32_t>(total_tiles), pixels, x->cu_count);
+    BatchLaunch l = batch_launch(tun, static_cast<uint32_t>(total_tiles), pixels, x->cu_count);
     l.n_streams = static_cast<uint32_t>(n);
     l.measure = measure;
     l.stream = streams_rows(hot);

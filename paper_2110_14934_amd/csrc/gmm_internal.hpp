@@ -66,8 +66,14 @@ struct BatchLaunch {
   bool stream;            // streams_rows of all streams' hot bytes together
 };
 constexpr gmm_batch_tuning kDefaultTuning{256, 1024, 8};
-// The launch shape for a tuning (`open`: the default, the shape left to the library).
-BatchLaunch batch_launch(const gmm_batch_tuning& t, bool open, uint32_t n_tiles, uint64_t pixels, int cu_count);
+// Whether a tuning leaves the shape to the library: the default does, whether a caller set it or not,
+// so that setting the tuning that was read back changes nothing.
+inline bool is_open(const gmm_batch_tuning& t) {
+  return t.block_threads == kDefaultTuning.block_threads && t.tile_pixels == kDefaultTuning.tile_pixels &&
+         t.blocks_per_cu == kDefaultTuning.blocks_per_cu;
+}
+// The launch shape for a tuning.
+BatchLaunch batch_launch(const gmm_batch_tuning& t, uint32_t n_tiles, uint64_t pixels, int cu_count);
 hipError_t launch_batch(int M, int dtype, const BatchLaunch& l, hipStream_t s);
 // Descriptors (and first tiles, unless NULL) of n streams to the device as kernel arguments, up to
 // kPackPerLaunch streams with equal model constants per launch, half as many with mixed ones.

@@ -176,7 +176,7 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
   hipStream_t hs = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   uint32_t next_first = 0;
-  BatchLaunch l = batch_launch(t, tuning == nullptr, static_cast<uint32_t>(total), pixels, cus);
+  BatchLaunch l = batch_launch(t, static_cast<uint32_t>(total), pixels, cus);
   l.table = table;
   l.first = first;
   l.n_streams = static_cast<uint32_t>(n);

@@ -344,12 +344,49 @@ static void detach() {
   OK(gmm_destroy(other));
 }
 
+// Setting the shape that a batch reports changes nothing; the static call takes the default shape and
+// no shape for the same thing.
+static void round_trip() {
+  gmm_handle* h[2] = {handle(640, 480), handle(320, 240)};
+  void* mem = nullptr;
+  (void)hipMalloc(&mem, 1 << 21);
+  uint8_t* d = static_cast<uint8_t*>(mem);
+  uint64_t* m = reinterpret_cast<uint64_t*>(mem);
+  const gmm_stream_io io[2] = {{d, 1920, reinterpret_cast<uint16_t*>(d), 1280, m, m + 4800, nullptr},
+                               {d, 960, reinterpret_cast<uint16_t*>(d), 640, m + 9600, m + 10800, nullptr}};
+  gmm_batch* b = nullptr;
+  OK(gmm_batch_create(h, 2, 1, &b));
+  const auto shape = [&] {
+    OK(gmm_batch_apply(b, io, nullptr));
+    return rt().launches.back();
+  };
+  const auto same = [](const Launch& x, const Launch& y) { return x.name == y.name && x.grid == y.grid && x.block == y.block; };
+  gmm_batch_tuning t{};
+  const Launch first = shape();
+  OK(gmm_batch_get_tuning(b, &t));
+  OK(gmm_batch_set_tuning(b, &t));
+  EXPECT(same(shape(), first));
+  const gmm_batch_tuning other{512, 2048, 1};
+  OK(gmm_batch_set_tuning(b, &other));
+  const Launch walking = shape();
+  EXPECT(walking.block == 512 && walking.grid == 150 + 38);  // a block per tile, fewer than CUs
+  OK(gmm_batch_set_tuning(b, &t));
+  EXPECT(same(shape(), first));
+  OK(gmm_batch_apply_static(h, 2, io, nullptr, nullptr));
+  const Launch open = rt().launches.back();
+  OK(gmm_batch_apply_static(h, 2, io, &t, nullptr));
+  EXPECT(same(rt().launches.back(), open));
+  OK(gmm_batch_destroy(b));
+  for (auto* g : h) OK(gmm_destroy(g));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
       {"coherence", coherence},
       {"overlap", overlap},
       {"detach", detach},
+      {"round_trip", round_trip},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);
