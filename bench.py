@@ -603,7 +603,7 @@ def bench_serve(args) -> int:
           f"{h2d['per_frame_copies_gbs']:.1f} GB/s frame by frame; demand at 30 fps "
           f"{h2d['demand_gbs']:.1f} GB/s", file=sys.stderr, flush=True)
     budget = int(args.serve_budget_gb * (1 << 30))
-    ex = NativeExecutor(ring=4, state_dtype=dtype, tuning=(256, 1024, 4), arena_bytes=budget)
+    ex = NativeExecutor(ring=4, state_dtype=dtype, arena_bytes=budget)
     srv = Server(ex, budget, max_queue=8)
     prog = lambda m: print("[serve] " + m, file=sys.stderr, flush=True)
     try:

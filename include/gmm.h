@@ -360,8 +360,9 @@ typedef struct {
 gmm_status gmm_exec_create(int32_t device, int32_t ring, gmm_exec** out);
 /* Wait for all ticks, then release. NULL is a no-op. Attached handles stay valid. */
 gmm_status gmm_exec_destroy(gmm_exec* x);
-/* Launch shape of the batched kernel (same meaning and limits as gmm_batch_tuning). Ticks that read
- * frames in place take the default shape. */
+/* Launch shape of the batched kernel (same meaning and limits as gmm_batch_tuning). In ticks that read
+ * frames in place every tile has a block of its own, and blocks_per_cu says how many of them a compute
+ * unit takes at a time. */
 gmm_status gmm_exec_set_tuning(gmm_exec* x, const gmm_batch_tuning* t);
 /* Give a stream two device frame slots, used by its frames in turn so that one frame can be
  * copied in while the previous one computes (all streams of an executor share M and the state

@@ -58,9 +58,9 @@ template <int M, typename S, int CP, bool MEASURE>
 static hipError_t launch_batch_mscm(const BatchLaunch& l, hipStream_t s) {
   const dim3 grid(l.grid);
   if (l.block == 256)
-    batch_kernel<M, S, 256, CP, MEASURE><<<grid, dim3(256), 0, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
+    batch_kernel<M, S, 256, CP, MEASURE><<<grid, dim3(256), l.lds, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
   else if (l.block == 512)
-    batch_kernel<M, S, 512, CP, MEASURE><<<grid, dim3(512), 0, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
+    batch_kernel<M, S, 512, CP, MEASURE><<<grid, dim3(512), l.lds, s>>>(l.table, l.first, l.n_streams, l.n_pieces, l.tile_px, l.piece_shift);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -113,10 +113,21 @@ BatchLaunch batch_launch(const gmm_batch_tuning& t, uint32_t n_tiles, uint64_t p
   l.tile_px = static_cast<uint32_t>(t.tile_pixels);
   l.piece_shift = !is_open(t) || n_tiles >= (1u << 28) ? 0u : (pixels < kSmallBatchPixels ? 2u : 1u);
   l.n_pieces = n_tiles << l.piece_shift;
-  const bool walk = t.blocks_per_cu * t.block_threads < 2048;
-  const uint32_t want = walk ? static_cast<uint32_t>(t.blocks_per_cu) * static_cast<uint32_t>(cu_count) : kMaxGrid;
+  const uint32_t want = walks(t) ? static_cast<uint32_t>(t.blocks_per_cu) * static_cast<uint32_t>(cu_count) : kMaxGrid;
   l.grid = std::max(1u, std::min(want, l.n_pieces));
   return l;
+}
+
+// Ticks that read frames over the host link (gmm_exec_launch) keep the caller's blocks per CU by what
+// a CU has room for, not by a grid of walking blocks: the dispatcher then gives the next piece to the
+// CU that is free, where a walking block whose loads come back late holds up all its pieces. The room
+// is LDS: each block reserves so much that no more than `blocks` fit. Ticks of 32 VGA fp16 streams and
+// of 16 fp32 ones with 4 blocks of 256 threads per CU: 1169 and 614 us walking, 1069 and 552 us so.
+void limit_residency(BatchLaunch& l, uint32_t blocks) {
+  constexpr uint32_t kLdsPerCu = 160u << 10, kGrain = 1280;
+  const uint32_t own = static_cast<uint32_t>(l.block) / kWave * 48u * 4u;
+  l.grid = std::min(kMaxGrid, l.n_pieces);
+  l.lds = (kLdsPerCu / (blocks + 1) / kGrain + 1) * kGrain - own;
 }
 
 struct PackWholeArgs {

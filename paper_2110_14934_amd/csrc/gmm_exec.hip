@@ -453,10 +453,6 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     if (e != hipSuccess) return fail(GMM_ERR_OUT_OF_MEMORY, "mask arena allocation failed");
     s.mask_cap = mask_total * 2;
   }
-  // A tick that reads frames over the link always takes the default shape, one block per piece:
-  // what is in flight then keeps the link busy, where fewer blocks that walk tiles do not (640
-  // mixed streams a tick: 52.3 GB/s, 38.5 with 4 blocks of 256 threads per CU).
-  if (linked) tun = kDefaultTuning;
   const uint32_t tile_px = static_cast<uint32_t>(tun.tile_pixels);
   s.outs.clear();
   uint32_t* h_first = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s.h_table) + tab);
@@ -510,6 +506,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
   }
   if (e == hipSuccess) {
     BatchLaunch l = batch_launch(tun, static_cast<uint32_t>(total_tiles), pixels, x->cu_count);
+    if (linked && walks(tun)) limit_residency(l, static_cast<uint32_t>(tun.blocks_per_cu));
     l.n_streams = static_cast<uint32_t>(n);
     l.measure = measure;
     l.stream = streams_rows(hot);

@@ -62,6 +62,7 @@ struct BatchLaunch {
   uint32_t piece_shift;   // a tile is 2^piece_shift pieces, one block each
   uint32_t grid;
   int block;              // threads per block
+  uint32_t lds = 0;       // bytes of LDS a block reserves beyond its own use (limit_residency)
   bool measure;           // some descriptor has a traffic record (wave_bytes): the kernel that counts bytes runs
   bool stream;            // streams_rows of all streams' hot bytes together
 };
@@ -72,8 +73,12 @@ inline bool is_open(const gmm_batch_tuning& t) {
   return t.block_threads == kDefaultTuning.block_threads && t.tile_pixels == kDefaultTuning.tile_pixels &&
          t.blocks_per_cu == kDefaultTuning.blocks_per_cu;
 }
+// Whether a tuning has fewer blocks per CU than a CU holds (2048 threads): its blocks walk tiles.
+inline bool walks(const gmm_batch_tuning& t) { return t.blocks_per_cu * t.block_threads < 2048; }
 // The launch shape for a tuning.
 BatchLaunch batch_launch(const gmm_batch_tuning& t, uint32_t n_tiles, uint64_t pixels, int cu_count);
+// One block per piece for `l`, with at most `blocks` of them on a CU at a time.
+void limit_residency(BatchLaunch& l, uint32_t blocks);
 hipError_t launch_batch(int M, int dtype, const BatchLaunch& l, hipStream_t s);
 // Descriptors (and first tiles, unless NULL) of n streams to the device as kernel arguments, up to
 // kPackPerLaunch streams with equal model constants per launch, half as many with mixed ones.

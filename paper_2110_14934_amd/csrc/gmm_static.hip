@@ -48,9 +48,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(M <
 template <int M, typename S>
 static hipError_t launch_args_ms(const PackArgs& p, const BatchLaunch& l, hipStream_t s) {
   if (l.stream)
-    batch_args_kernel<M, S, kStream><<<dim3(l.grid), dim3(kBlock), 0, s>>>(p, l.tile_px, l.piece_shift);
+    batch_args_kernel<M, S, kStream><<<dim3(l.grid), dim3(kBlock), l.lds, s>>>(p, l.tile_px, l.piece_shift);
   else
-    batch_args_kernel<M, S, kCached><<<dim3(l.grid), dim3(kBlock), 0, s>>>(p, l.tile_px, l.piece_shift);
+    batch_args_kernel<M, S, kCached><<<dim3(l.grid), dim3(kBlock), l.lds, s>>>(p, l.tile_px, l.piece_shift);
   return hipGetLastError();
 }
 

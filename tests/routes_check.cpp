@@ -380,6 +380,45 @@ static void round_trip() {
   for (auto* g : h) OK(gmm_destroy(g));
 }
 
+// A launch shape set on an executor holds for ticks that read page-locked frames too: its threads and
+// tiles as they are, its blocks per CU as the number that a CU has LDS for.
+static void exec_tuning() {
+  constexpr int W = 1024, H = 1024;
+  constexpr size_t px = size_t(W) * H, kLdsPerCu = 160 << 10;
+  gmm_exec* x = nullptr;
+  OK(gmm_exec_create(0, 2, &x));
+  gmm_handle* h = handle(W, H);
+  OK(gmm_exec_attach(x, h, nullptr));
+  uint64_t* m = reinterpret_cast<uint64_t*>(pinned(3 * px / 8));
+  uint8_t* rgb = pinned(px * 3);
+  uint16_t* depth = reinterpret_cast<uint16_t*>(pinned(px * 2));
+  const std::vector<gmm_exec_item> it{{h, rgb, depth, m, m + px / 64, m + 2 * (px / 64)}};
+  for (int threads : {256, 512})
+    for (int tiles : {1, 4})
+      for (int per_cu = 1; per_cu <= 32; ++per_cu) {
+        const gmm_batch_tuning t{threads, threads * tiles, per_cu};
+        if (threads == 256 && tiles == 4 && per_cu == 8) continue;  // the default
+        OK(gmm_exec_set_tuning(x, &t));
+        const Counts n = tick(x, it);
+        const Launch& l = rt().launches.back();
+        const size_t own = static_cast<size_t>(threads) / 64 * 192;
+        const bool shaped = l.block == static_cast<unsigned>(threads) && l.grid == px / t.tile_pixels;
+        const bool held = per_cu * threads >= 2048 ? l.lds == 0 : kLdsPerCu / (l.lds + own) == static_cast<size_t>(per_cu);
+        if (!shaped || !held || n.h2d || n.d2h)
+          std::printf("{%d, %d, %d}: %u blocks of %u threads, %zu bytes of LDS, %zu frames copied\n", threads, t.tile_pixels,
+                      per_cu, l.grid, l.block, l.lds, n.h2d), ++g_bad;
+      }
+  // frames that are copied leave the kernel's blocks walking, as a batch's do
+  const gmm_batch_tuning t{256, 1024, 2};
+  OK(gmm_exec_set_tuning(x, &t));
+  std::vector<uint8_t> c(px * 3);
+  std::vector<uint16_t> d(px);
+  const Counts n = tick(x, {{h, c.data(), d.data(), m, nullptr, nullptr}});
+  EXPECT(n.h2d == 2 && rt().launches.back().grid == 512 && rt().launches.back().lds == 0);
+  OK(gmm_exec_destroy(x));
+  OK(gmm_destroy(h));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
@@ -387,6 +426,7 @@ int main(int argc, char** argv) {
       {"overlap", overlap},
       {"detach", detach},
       {"round_trip", round_trip},
+      {"exec_tuning", exec_tuning},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);
