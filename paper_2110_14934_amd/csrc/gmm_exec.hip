@@ -229,6 +229,15 @@ static bool masks_apart(std::vector<Buffer>& b) {
   return true;
 }
 
+// Blocks that a tick reading frames in place keeps on a CU, with the default shape. Such a tick lasts as
+// long as its frames take over the link (500 us for 16 VGA streams, of which the kernel would need 85),
+// and blocks that filled the CUs all that time kept other work off the device: a batch of 16 VGA fp32
+// streams, 90 us alone, took 620 us beside ticks, a 4096 bf16 matrix product 615 us instead of 134.
+// Two blocks of 256 threads read as fast (16 VGA fp16 streams 503 us a tick, 516 with full CUs; 12 fp32
+// streams 395 and 398; all pixels changing 535 and 577) and leave the batch at 138 us, the product at
+// 223. One block is slower where fp32 rows move (405 us for the 12 streams), three let 450 us pass.
+constexpr uint32_t kLinkBlocksPerCu = 2;
+
 static size_t mask_bytes(const gmm_handle* h) { return static_cast<size_t>((h->npix + 63) / 64) * 8; }
 
 extern "C" {
@@ -506,7 +515,8 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
   }
   if (e == hipSuccess) {
     BatchLaunch l = batch_launch(tun, static_cast<uint32_t>(total_tiles), pixels, x->cu_count);
-    if (linked && walks(tun)) limit_residency(l, static_cast<uint32_t>(tun.blocks_per_cu));
+    if (linked && (walks(tun) || is_open(tun)))
+      limit_residency(l, is_open(tun) ? kLinkBlocksPerCu : static_cast<uint32_t>(tun.blocks_per_cu));
     l.n_streams = static_cast<uint32_t>(n);
     l.measure = measure;
     l.stream = streams_rows(hot);

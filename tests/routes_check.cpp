@@ -419,6 +419,32 @@ static void exec_tuning() {
   OK(gmm_destroy(h));
 }
 
+// A tick that waits for the host link leaves most of every CU to other work: no more than two of its
+// blocks of 256 threads on a CU, and a quarter of its LDS free.
+static void residency() {
+  constexpr size_t kLdsPerCu = 160 << 10;
+  gmm_exec* x = nullptr;
+  OK(gmm_exec_create(0, 2, &x));
+  std::vector<gmm_handle*> h;
+  std::vector<gmm_exec_item> in_place, copied;
+  constexpr int W = 64, H = 64;
+  static uint8_t rgb[W * H * 3];
+  for (int i = 0; i < 40; ++i) {  // up to 32 streams' descriptors travel with the kernel, more in a table
+    h.push_back(handle(W, H, GMM_RGB));
+    OK(gmm_exec_attach(x, h.back(), nullptr));
+    in_place.push_back({h.back(), pinned(sizeof rgb), nullptr, reinterpret_cast<uint64_t*>(pinned(W * H / 8)), nullptr, nullptr});
+    copied.push_back({h.back(), rgb, nullptr, nullptr, nullptr, nullptr});
+    if (i + 1 != 1 && i + 1 != 32 && i + 1 != 40) continue;
+    (void)tick(x, in_place);
+    const Launch l = rt().launches.back();
+    EXPECT(l.block == 256 && kLdsPerCu / (l.lds + 768) == 2 && kLdsPerCu - 2 * (l.lds + 768) >= kLdsPerCu / 4);
+    (void)tick(x, copied);
+    EXPECT(rt().launches.back().lds == 0);
+  }
+  OK(gmm_exec_destroy(x));
+  for (auto* g : h) OK(gmm_destroy(g));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
@@ -427,6 +453,7 @@ int main(int argc, char** argv) {
       {"detach", detach},
       {"round_trip", round_trip},
       {"exec_tuning", exec_tuning},
+      {"residency", residency},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);
