@@ -1,6 +1,7 @@
 // The C ABI (include/gmm.h): validation, state ownership, dispatch, state snapshots.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -140,6 +141,8 @@ gmm_status rgbd::new_handle(const gmm_config* cfg, gmm_handle** out) {
   // one flags byte per pixel for a handle with a depth model: its List 1 state (two modalities)
   // and its hole count (fp32 state)
   h->fuse_bytes = sep_depth(h) ? static_cast<size_t>(round_up(h->npix, 256)) : 0;
+  h->hot = static_cast<size_t>(h->npix) * ((has_rgb(h) ? tile_layout(M, is_augmented(h) ? 4 : 3, es).hot + 3 : 0) +
+                                           (sep_depth(h) ? tile_layout(M, 1, es).hot + 1 : 0) + (has_depth(h) ? 2 : 0));
   // below 2 GiB: the kernels address a block with 32-bit offsets and use offset 2^31 for "no access"
   if (std::max(h->rgb_bytes, h->depth_bytes) >= 0x80000000ull) {
     delete h;
@@ -174,11 +177,19 @@ hipError_t rgbd::init_state(gmm_handle* h, hipStream_t s) {
   return e;
 }
 
-size_t rgbd::hot_bytes(const gmm_handle* h) {
-  const uint32_t M = static_cast<uint32_t>(h->cfg.M), es = static_cast<uint32_t>(h->esize);
-  const size_t rgb = !has_rgb(h) ? 0 : tile_layout(M, is_augmented(h) ? 4 : 3, es).hot + 3;
-  const size_t depth = !has_depth(h) ? 0 : (sep_depth(h) ? tile_layout(M, 1, es).hot + 1 : 0) + 2;
-  return static_cast<size_t>(h->npix) * (rgb + depth);
+// Hot bytes that the launches on each device have gone through (it only chooses a cache policy, so
+// devices whose ordinals share an entry and launches of other threads at the same time do no harm).
+static std::atomic<uint64_t> g_touched[64];
+
+bool rgbd::streams_rows(gmm_handle* const* h, size_t n) {
+  size_t hot = 0, far = 0;
+  for (size_t i = 0; i < n; ++i) hot += h[i]->hot;
+  const uint64_t now = g_touched[h[0]->cfg.device % 64].fetch_add(hot, std::memory_order_relaxed) + hot;
+  for (size_t i = 0; i < n; ++i) {
+    if ((h[i]->touched ? now - h[i]->touched : hot) >= kStreamHotBytes) far += h[i]->hot;
+    h[i]->touched = now;
+  }
+  return 2 * far > hot;
 }
 
 size_t rgbd::state_bytes(const gmm_handle* h) { return h->rgb_bytes + h->depth_bytes + h->fuse_bytes; }
@@ -344,7 +355,7 @@ gmm_status gmm_apply_frame(gmm_handle* h, const uint8_t* rgb, int64_t rgb_pitch_
   const FrameArgs a = frame_args(h, rgb, rgb_pitch_bytes, depth, depth_pitch_bytes, fg_rgb, fg_depth, nullptr);
   const int mode = (has_rgb(h) ? kModeRGB : 0) | (has_depth(h) ? kModeDepth : 0);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, mode, streams_rows(hot_bytes(h)), s);
+  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, mode, streams_rows(&h, 1), s);
   if (e != hipSuccess) return hip_fail(e, "frame kernel launch");
   h->last_stream = s;
   return GMM_OK;
@@ -381,7 +392,7 @@ gmm_status gmm_apply_frame_fused(gmm_handle* h, const uint8_t* rgb, int64_t rgb_
   if (!g.ok()) return fail(GMM_ERR_DEVICE, "cannot select the handle's device");
   const FrameArgs a = frame_args(h, rgb, rgb_pitch_bytes, depth, depth_pitch_bytes, fg_rgb, fg_depth, fused);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, kModeRGB | kModeDepth | kModeFuse, streams_rows(hot_bytes(h)), s);
+  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, kModeRGB | kModeDepth | kModeFuse, streams_rows(&h, 1), s);
   if (e != hipSuccess) return hip_fail(e, "fused frame kernel launch");
   h->last_stream = s;
   return GMM_OK;
@@ -403,7 +414,7 @@ gmm_status gmm_apply_frame_augmented(gmm_handle* h, const uint8_t* rgb, int64_t 
   if (!g.ok()) return fail(GMM_ERR_DEVICE, "cannot select the handle's device");
   const FrameArgs a = frame_args(h, rgb, rgb_pitch_bytes, depth, depth_pitch_bytes, fg, nullptr, nullptr);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, kModeAug, streams_rows(hot_bytes(h)), s);
+  hipError_t e = launch_frame(a, h->cfg.M, h->cfg.state_dtype, kModeAug, streams_rows(&h, 1), s);
   if (e != hipSuccess) return hip_fail(e, "augmented frame kernel launch");
   h->last_stream = s;
   return GMM_OK;

@@ -205,7 +205,6 @@ struct gmm_batch {
   uint32_t* d_first_tile = nullptr;
   uint32_t n_tiles = 0;
   uint64_t pixels = 0;                       // of one frame of every stream
-  size_t hot = 0;                            // hot_bytes of all streams
   gmm_batch_tuning tuning = kDefaultTuning;
   hipStream_t last_stream = nullptr;
 };
@@ -228,12 +227,10 @@ static gmm_status build_tiles(gmm_batch* b, uint32_t tile_px) {
   std::vector<uint32_t> first(n_streams(b));
   uint64_t total = 0;
   b->pixels = 0;
-  b->hot = 0;
   for (size_t i = 0; i < n_streams(b); ++i) {
     first[i] = static_cast<uint32_t>(total);
     total += (static_cast<uint64_t>(b->handles[i]->npix) + tile_px - 1) / tile_px;
     b->pixels += static_cast<uint64_t>(b->handles[i]->npix);
-    b->hot += hot_bytes(b->handles[i]);
   }
   if (total >= (1ull << 31)) return fail(GMM_ERR_INVALID_ARG, "too many tiles in one batch");
   const hipError_t e = hipMemcpy(b->d_first_tile, first.data(), first.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
@@ -257,7 +254,7 @@ static hipError_t run_slot(gmm_batch* b, int slot, hipStream_t s) {
   l.first = b->d_first_tile;
   l.n_streams = static_cast<uint32_t>(n_streams(b));
   l.measure = b->slot_measure[slot] != 0;
-  l.stream = streams_rows(b->hot);
+  l.stream = streams_rows(b->handles.data(), n_streams(b));
   return launch_batch(b->M, b->dtype, l, s);
 }
 

@@ -55,7 +55,6 @@ struct Attached {
   uint8_t* d_rgb[kFramesInFlight] = {};        // dense colour slots (3 bytes per pixel)
   uint16_t* d_depth[kFramesInFlight] = {};     // dense depth slots (2 bytes per pixel)
   size_t bytes = 0;
-  size_t hot = 0;                              // hot_bytes of the stream
   int in_flight = 0;
   uint64_t frames = 0;                         // frames launched; frame f uses slot f % 2
 };
@@ -109,7 +108,6 @@ struct gmm_exec {
   hipStream_t s_compute = nullptr, s_out = nullptr;
   std::vector<Slot> slots;
   std::map<const gmm_handle*, Attached> attached;
-  size_t hot = 0;  // hot_bytes of the attached streams: what competes for the last-level cache between a stream's frames
   uint64_t next_tick = 1;
   // completion thread
   std::mutex mu;
@@ -318,9 +316,7 @@ gmm_status gmm_exec_attach(gmm_exec* x, gmm_handle* h, size_t* device_bytes) {
   a.base = mem;
   place_slots(a, h, static_cast<uint8_t*>(mem));
   a.bytes = slots;
-  a.hot = hot_bytes(h);
   x->attached[h] = a;
-  x->hot += a.hot;
   x->M = h->cfg.M;
   x->dtype = h->cfg.state_dtype;
   if (device_bytes) *device_bytes = a.bytes;
@@ -334,7 +330,6 @@ gmm_status gmm_exec_detach(gmm_exec* x, gmm_handle* h) {
   if (it == x->attached.end()) return fail(GMM_ERR_INVALID_ARG, "handle not attached");
   x->cv.wait(lk, [&] { return it->second.in_flight == 0; });  // its last frame has completed
   void* base = it->second.base;
-  x->hot -= it->second.hot;
   x->attached.erase(it);
   lk.unlock();
   DeviceGuard g(x->device);
@@ -376,12 +371,12 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     std::unique_lock<std::mutex> lk(x->mu);
     x->cv.wait(lk, [&] { return !s.busy; });
   }
+  s.handles.clear();
+  for (int32_t i = 0; i < n; ++i) s.handles.push_back(items[i].handle);
   gmm_batch_tuning tun;
-  size_t hot;
   {
     std::lock_guard<std::mutex> lk(x->mu);
     tun = x->tuning;
-    hot = x->hot;
   }
   // work list: n descriptors followed by n tile starts
   const size_t tab = static_cast<size_t>(n) * sizeof(FrameArgs);
@@ -519,7 +514,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
       limit_residency(l, is_open(tun) ? kLinkBlocksPerCu : static_cast<uint32_t>(tun.blocks_per_cu));
     l.n_streams = static_cast<uint32_t>(n);
     l.measure = measure;
-    l.stream = streams_rows(hot);
+    l.stream = streams_rows(s.handles.data(), s.handles.size());
     if (fits_args(s.h_table, l)) {
       e = launch_batch_args(x->M, x->dtype, s.h_table, h_first, l, x->s_compute);
     } else {
@@ -548,9 +543,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     std::lock_guard<std::mutex> lk(x->mu);
     s.tick = tick;
     s.busy = true;
-    s.handles.clear();
     for (int32_t i = 0; i < n; ++i) {
-      s.handles.push_back(items[i].handle);
       Attached& a = x->attached[items[i].handle];
       a.in_flight++;
       a.frames++;
@@ -609,9 +602,7 @@ gmm_status gmm_exec_create_stream(gmm_exec* x, const gmm_config* cfg, void* mem,
     return hip_fail(e, "state initialisation");
   }
   h->last_stream = x->s_compute;
-  a.hot = hot_bytes(h);
   x->attached[h] = a;
-  x->hot += a.hot;
   x->M = h->cfg.M;
   x->dtype = h->cfg.state_dtype;
   *out = h;
@@ -625,7 +616,6 @@ gmm_status gmm_exec_destroy_stream(gmm_exec* x, gmm_handle* h) {
   auto it = x->attached.find(h);
   if (it == x->attached.end()) return fail(GMM_ERR_INVALID_ARG, "handle not attached");
   x->cv.wait(lk, [&] { return it->second.in_flight == 0; });  // its last frame has completed
-  x->hot -= it->second.hot;
   x->attached.erase(it);
   lk.unlock();
   delete h;

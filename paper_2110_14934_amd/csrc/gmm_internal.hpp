@@ -41,7 +41,7 @@ enum FrameMode : int { kModeRGB = 1, kModeDepth = 2, kModeFuse = 4, kModeAug = 8
 
 // Launchers (return hipSuccess or the launch error).
 // `stream`: the kernel's rows take the non-temporal cache policy (kStream), for streams
-// whose hot bytes cannot stay in the last-level cache between frames (streams_rows).
+// whose rows cannot stay in the last-level cache between frames (streams_rows).
 hipError_t launch_frame(const FrameArgs& a, int M, int dtype, int mode, bool stream, hipStream_t s);
 hipError_t launch_fuse(const uint64_t* fr, const uint64_t* fd, uint64_t* out, uint8_t* fstate,
                        int64_t npix, hipStream_t s);
@@ -64,7 +64,7 @@ struct BatchLaunch {
   int block;              // threads per block
   uint32_t lds = 0;       // bytes of LDS a block reserves beyond its own use (limit_residency)
   bool measure;           // some descriptor has a traffic record (wave_bytes): the kernel that counts bytes runs
-  bool stream;            // streams_rows of all streams' hot bytes together
+  bool stream;            // streams_rows of the streams
 };
 constexpr gmm_batch_tuning kDefaultTuning{256, 1024, 8};
 // Whether a tuning leaves the shape to the library: the default does, whether a caller set it or not,
@@ -138,6 +138,8 @@ struct gmm_handle {  // the library's per-stream object (opaque in gmm.h)
   void* st_depth = nullptr;
   uint8_t* fstate = nullptr;
   hipStream_t last_stream = nullptr;
+  size_t hot = 0;           // bytes that every frame touches: hot rows, frames and flags
+  uint64_t touched = 0;     // hot bytes that the device's launches had gone through after its last frame (streams_rows)
   rgbd::ModelConsts kc{}, kd{};
 };
 
@@ -164,12 +166,17 @@ void place_state(gmm_handle* h, void* mem);
 // Enqueue the initial (all components empty) state on `s`.
 hipError_t init_state(gmm_handle* h, hipStream_t s);
 size_t state_bytes(const gmm_handle* h);
-// Bytes of a stream that every frame touches: its hot rows, its frames and its flags.
-size_t hot_bytes(const gmm_handle* h);
-// Whether a launch over `hot` such bytes streams its rows: from half the 256 MB last-level cache
-// up. Batches of VGA streams, rows kept against rows streamed: fp32, 8 streams (110 MB hot) 41.7
-// and 43.7 us, 12 streams (165 MB) 63.8 and 60.4 us; fp16, 10 streams (123 MB) 45.9 and 48.4 us, 12
-// (148 MB) 59.1 and 57.7 us.
-constexpr size_t kStreamHotBytes = size_t(128) << 20;
-inline bool streams_rows(size_t hot) { return hot >= kStreamHotBytes; }
+// Whether a launch that advances these `n` streams of one device by one frame streams their rows;
+// notes the launch. Rows kept in the last-level cache (256 MB) are there for a stream's next frame
+// only if less than that has gone through it since: what counts is the hot bytes of all launches on
+// the device between two frames of a stream, its own included, however they are divided into
+// streams, batches and ticks. A stream's first frame counts its launch alone. The launch takes the
+// policy that is right for the larger part of its bytes. Rows kept against rows streamed, us a call:
+// one batch of VGA fp32 streams, 12 (170 MB) 47.5 and 54.9, 16 (226 MB) 68.8 and 72.2, 24 (339 MB)
+// 109.0 and 105.6; single 1920x1080 fp32 streams in turn, 2 (191 MB) 27.5 and 28.3, 3 (286 MB) 28.5
+// and 28.8, 4 (382 MB) 33.0 and 28.9; 64 VGA streams in turn 8.9 and 7.7; batches of 8 VGA streams in turn,
+// 2 (226 MB) 37.2 and 38.8, 3 (339 MB) 41.1 and 39.4, 4 45.6 and 39.6; 64 VGA fp16 streams in turn
+// 9.4 and 8.0.
+constexpr size_t kStreamHotBytes = size_t(256) << 20;
+bool streams_rows(gmm_handle* const* h, size_t n);
 }  // namespace rgbd

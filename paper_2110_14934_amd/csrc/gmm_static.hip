@@ -145,7 +145,6 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
   for (int32_t i = 1; i < n; ++i)
     if (sorted[i] == sorted[i - 1]) return fail(GMM_ERR_INVALID_ARG, "a handle appears twice");
   uint64_t total = 0, pixels = 0;
-  size_t hot = 0;
   for (int32_t i = 0; i < n; ++i) {
     gmm_handle* h = handles[i];
     const gmm_stream_io& s = io[i];
@@ -161,7 +160,6 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
     }
     total += (static_cast<uint64_t>(h->npix) + t.tile_pixels - 1) / t.tile_pixels;
     pixels += static_cast<uint64_t>(h->npix);
-    hot += hot_bytes(h);
   }
   if (total >= (1ull << 31)) return fail(GMM_ERR_INVALID_ARG, "too many tiles in one launch");
   const int dev = handles[0]->cfg.device;
@@ -180,7 +178,7 @@ extern "C" gmm_status gmm_batch_apply_static(gmm_handle* const* handles, int32_t
   l.table = table;
   l.first = first;
   l.n_streams = static_cast<uint32_t>(n);
-  l.stream = streams_rows(hot);
+  l.stream = streams_rows(handles, static_cast<size_t>(n));
   bool packed = true;
   for (int32_t b = 0; b < n && e == hipSuccess; b += kPackPerLaunch) {
     FrameArgs a[kPackPerLaunch];

@@ -309,14 +309,15 @@ static void overlap() {
   for (auto* g : h) OK(gmm_destroy(g));
 }
 
-// The policy (CP) of the last batched launch: 0 rows kept in the caches, 2 rows streamed.
+// The policy (CP) of the last frame or batched launch: 0 rows kept in the caches, 2 rows streamed.
 static int policy() {
   for (size_t i = rt().launches.size(); i-- > 0;) {
     const std::string k = rt().launches[i].name.substr(0, rt().launches[i].name.find('('));
     const size_t last = k.rfind(',');
-    if (k.find("batch_args_kernel<") != std::string::npos) return std::atoi(k.c_str() + last + 1);  // <M, S, CP>
     if (k.find("batch_kernel<") != std::string::npos)  // <M, S, BLOCK, CP, MEASURE>
       return std::atoi(k.c_str() + k.rfind(',', last - 1) + 1);
+    if (k.find("batch_args_kernel<") != std::string::npos || k.find("frame_kernel<") != std::string::npos)
+      return std::atoi(k.c_str() + last + 1);  // <..., CP>
   }
   return -1;
 }
@@ -445,6 +446,64 @@ static void residency() {
   for (auto* g : h) OK(gmm_destroy(g));
 }
 
+// Rows are kept in the 256 MB last-level cache if they are still there when the stream's next frame
+// comes: what other launches on the device go through in between counts, whatever they belong to.
+static void cache_policy() {
+  constexpr int W = 640, H = 480;  // 307200 pixels, 46 hot bytes each: 14.1 MB
+  void* mem = nullptr;
+  (void)hipMalloc(&mem, 1 << 21);
+  uint8_t* d = static_cast<uint8_t*>(mem);
+  uint64_t* m = reinterpret_cast<uint64_t*>(mem);
+  const gmm_stream_io io{d, 3 * W, reinterpret_cast<uint16_t*>(d), 2 * W, m, m + 4800, nullptr};
+  const std::vector<gmm_stream_io> ios(40, io);
+  std::vector<gmm_handle*> h;
+  for (int i = 0; i < 40; ++i) h.push_back(handle(W, H));
+  const auto frame = [&](gmm_handle* g) {
+    OK(gmm_apply_frame(g, d, 3 * W, reinterpret_cast<uint16_t*>(d), 2 * W, m, m + 4800, nullptr));
+    return policy();
+  };
+  // single streams: 16 in turn stay in the cache (226 MB), 24 do not, one of them alone does again
+  for (int i = 0; i < 32; ++i) EXPECT(frame(h[i % 16]) == 0);
+  for (int i = 0; i < 72; ++i) EXPECT(frame(h[i % 24]) == 2 || i < 24);
+  for (int i = 0; i < 4; ++i) EXPECT(frame(h[23]) == 0);
+  // one batch of 16, of 24; two of 8 in turn, four of 8 in turn, by either batched call
+  const auto batches = [&](int count, int each, bool fixed) {
+    std::vector<gmm_batch*> b(count);
+    int last = -1;
+    for (int i = 0; i < count; ++i) OK(gmm_batch_create(h.data() + i * each, each, 1, &b[i]));
+    for (int t = 0; t < 3; ++t)
+      for (int i = 0; i < count; ++i) {
+        if (fixed) OK(gmm_batch_apply_static(h.data() + i * each, each, ios.data(), nullptr, nullptr));
+        else OK(gmm_batch_apply(b[i], ios.data(), nullptr));
+        last = policy();
+      }
+    for (auto* x : b) OK(gmm_batch_destroy(x));
+    return last;
+  };
+  for (bool fixed : {false, true}) {
+    EXPECT(batches(1, 16, fixed) == 0);
+    EXPECT(batches(1, 24, fixed) == 2);
+    EXPECT(batches(2, 8, fixed) == 0);
+    EXPECT(batches(4, 8, fixed) == 2);
+  }
+  // two executors, 12 streams each, each stream in turn; then one stream of them alone
+  gmm_exec* x[2] = {};
+  for (auto& e : x) OK(gmm_exec_create(0, 2, &e));
+  for (int i = 0; i < 24; ++i) OK(gmm_exec_attach(x[i % 2], h[i], nullptr));
+  uint8_t* rgb = pinned(W * H * 3);
+  uint16_t* depth = reinterpret_cast<uint16_t*>(pinned(W * H * 2));
+  for (int i = 0; i < 72; ++i) {
+    (void)tick(x[i % 2], {{h[i % 24], rgb, depth, nullptr, nullptr, nullptr}});
+    EXPECT(i < 24 || policy() == 2);
+  }
+  for (int i = 0; i < 4; ++i) {
+    (void)tick(x[1], {{h[23], rgb, depth, nullptr, nullptr, nullptr}});
+    EXPECT(policy() == 0);
+  }
+  for (auto* e : x) OK(gmm_exec_destroy(e));
+  for (auto* g : h) OK(gmm_destroy(g));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
@@ -454,6 +513,7 @@ int main(int argc, char** argv) {
       {"round_trip", round_trip},
       {"exec_tuning", exec_tuning},
       {"residency", residency},
+      {"cache_policy", cache_policy},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);
