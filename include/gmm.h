@@ -203,8 +203,8 @@ gmm_status gmm_state_size(const gmm_handle* h, size_t* n_doubles);
  * that kept its state through k missing readings carries the factor (1/(1-alpha))^k besides.
  * The canonical weight is the fp32 product of scale and factor (as the kernels form it) times
  * the scaled weight, exact in float64. Every other value is copied exactly. The values are
- * converted on the device through one 8 MB buffer of the library per device: reads and writes of
- * states on one device wait for each other.
+ * converted on the device through a 16 MB buffer of the library per device, which reads
+ * and writes at the same time share (one waits when all of it is taken).
  */
 gmm_status gmm_read_state(gmm_handle* h, double* host_out, void* stream);
 
@@ -212,7 +212,8 @@ gmm_status gmm_read_state(gmm_handle* h, double* host_out, void* stream);
  * Replace the state from the canonical layout (host memory, float64), rounding each value to
  * the storage type to nearest, ties to even (fp32 weights are stored with scale 1 and no
  * missing-reading factor, so a read followed by a write can change the low bits of the
- * weights). I must be 0 or 1 and cpt in [-3, 3], else GMM_ERR_INVALID_ARG. Synchronises `stream`.
+ * weights). I must be 0 or 1 and cpt in [-3, 3], else GMM_ERR_INVALID_ARG and the state is as it
+ * was; GMM_ERR_DEVICE can leave it partly written. Synchronises `stream`.
  */
 gmm_status gmm_write_state(gmm_handle* h, const double* host_in, void* stream);
 

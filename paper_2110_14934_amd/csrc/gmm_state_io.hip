@@ -6,14 +6,15 @@
 // 512 B), the state side is 4- or 2-byte pieces at the row's or the suffix's lane stride, merged
 // in the caches. What bounds the call is the host side: the canonical state (336 B per pixel of a
 // paired stream at M = 5) crosses the link and is written to pageable memory. The elements go
-// through one static device buffer, kChunk at a time, so a call allocates nothing and cannot run
-// out of device memory; ~8 MB is where the pageable copies stop getting faster (26 MB to the host
-// in 1.5 ms and from it in 0.96 ms, in pieces of 4 MB or more; 1.6 and 0.99 ms in pieces of 1 MB).
-// The conversion used to run on one host thread, value by value: a write, a frame and a read of a 320x240
-// paired stream (M = 5, fp32) took 49.5 ms; it takes 3.1 ms.
+// through a static device buffer, a piece at a time, so a call allocates nothing and cannot run out of
+// device memory. A call alone has 8 MB of it, where the pageable copies stop getting faster: a write
+// and a read of a 320x240 paired stream (M = 5, fp32; 25.8 MB each way) take 2.53 ms, in pieces of 4 MB
+// 2.74. The conversion used to run on one host thread, value by value: with a frame between them they
+// took 49.5 ms and take 2.6.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <condition_variable>
 #include <mutex>
 
 #include "gmm.h"
@@ -21,8 +22,9 @@
 
 namespace rgbd {
 
-constexpr uint32_t kChunk = 1u << 20;  // canonical elements in the buffer
-static __device__ __align__(256) double io_buffer[kChunk];
+constexpr uint32_t kSegment = 1u << 17;  // canonical elements
+constexpr uint32_t kSegments = 16;
+static __device__ __align__(256) double io_buffer[kSegments * kSegment];
 
 // Value k (parameter-major, rank within) of pixel p lies at base + (p / 64) tile + (p % 64) lane.
 struct ValueMap {
@@ -145,22 +147,24 @@ __global__ void __launch_bounds__(kBlock) unit_scale_kernel(float* __restrict__ 
   if (i < tiles64) scale[i] = 1.f;
 }
 
-// List 1 elements [e0, e0 + count): the fused bit of every pixel, then its counter.
-__global__ void __launch_bounds__(kBlock) unpack_fuse_kernel(const uint8_t* __restrict__ flags, uint32_t npix,
-                                                             double* __restrict__ out, uint32_t e0, uint32_t count) {
+// List 1 elements: the fused bits (BIT) or the counters of pixels [p0, p0 + count).
+template <bool BIT>
+__global__ void __launch_bounds__(kBlock) unpack_fuse_kernel(const uint8_t* __restrict__ flags, double* __restrict__ out,
+                                                             uint32_t p0, uint32_t count) {
   const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= count) return;
-  const uint32_t e = e0 + i;
-  const int v = e < npix ? (flags[e] >> 3) & 1 : static_cast<int>(flags[e - npix] & 7u) - 3;
-  out[i] = static_cast<double>(v);
+  const uint32_t f = flags[p0 + i];
+  out[i] = static_cast<double>(BIT ? static_cast<int>((f >> 3) & 1u) : static_cast<int>(f & 7u) - 3);
 }
 
-// Flags of `count` pixels from their fused bits (in[0 ..)) and counters (in[count ..)); no holes counted.
+template <bool BIT>
 __global__ void __launch_bounds__(kBlock) pack_fuse_kernel(uint8_t* __restrict__ flags, const double* __restrict__ in,
-                                                           uint32_t count) {
+                                                           uint32_t p0, uint32_t count) {
   const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= count) return;
-  flags[i] = static_cast<uint8_t>((static_cast<int>(in[count + i]) + 3) | (static_cast<int>(in[i]) << 3));
+  const uint32_t f = flags[p0 + i];
+  const int v = static_cast<int>(in[i]);
+  flags[p0 + i] = static_cast<uint8_t>(BIT ? (f & ~8u) | static_cast<uint32_t>(v) << 3 : (f & ~7u) | static_cast<uint32_t>(v + 3));
 }
 
 static inline dim3 blocks_for(uint32_t n) { return dim3((n + kBlock - 1) / kBlock); }
@@ -178,11 +182,53 @@ static hipError_t launch_pack(void* block, const BlockMap& b, const double* in, 
   return hipGetLastError();
 }
 
-// The buffer of the current device and the lock of its users. A call holds the lock until its
-// stream has drained; it synchronises the stream once before taking it, so that it never waits
-// for other work with the lock held.
-constexpr int kLocks = 64;
-static std::mutex g_io_mu[kLocks];
+// A call's part of the current device's buffer: adjacent segments, as many as its `elements` fill, but
+// at most half of those that are free, given back when the call ends. A call synchronises its stream
+// before it takes them, so that it never waits for other work while others wait for it, and again
+// before it gives them back. A call waits only when all segments are taken. 16 threads, a write and a
+// read of a 64x48 state each: 0.77 ms; 3.9 with one buffer and a lock, 2.4 when each converted on the
+// host. Of a 640x480 state: 59, 229 and 268 ms.
+constexpr int kDevices = 64;
+struct Segments {
+  std::mutex mu;
+  std::condition_variable given_back;
+  uint32_t used = 0;  // a bit per segment
+};
+static Segments g_io[kDevices];
+
+class IoSegments {
+ public:
+  IoSegments(int device, uint64_t elements) : io_(g_io[device % kDevices]) {
+    constexpr uint32_t kAll = (1u << kSegments) - 1u;
+    std::unique_lock<std::mutex> lk(io_.mu);
+    io_.given_back.wait(lk, [&] { return io_.used != kAll; });
+    const uint32_t half = std::max(1, __builtin_popcount(kAll & ~io_.used) / 2);
+    for (uint32_t n = static_cast<uint32_t>(std::min<uint64_t>(half, (elements + kSegment - 1) / kSegment)); mask_ == 0; --n)
+      for (uint32_t at = 0; at + n <= kSegments && mask_ == 0; ++at) {
+        const uint32_t m = ((1u << n) - 1u) << at;
+        if (io_.used & m) continue;
+        mask_ = m;
+        first_ = at;
+        count_ = n;
+      }
+    io_.used |= mask_;
+  }
+  ~IoSegments() {
+    {
+      std::lock_guard<std::mutex> lk(io_.mu);
+      io_.used &= ~mask_;
+    }
+    io_.given_back.notify_all();
+  }
+  IoSegments(const IoSegments&) = delete;
+  IoSegments& operator=(const IoSegments&) = delete;
+  double* in(double* buffer) const { return buffer + static_cast<size_t>(first_) * kSegment; }
+  uint32_t elements() const { return count_ * kSegment; }
+
+ private:
+  Segments& io_;
+  uint32_t mask_ = 0, first_ = 0, count_ = 0;
+};
 
 static hipError_t io_address(double** p) {
   void* a = nullptr;
@@ -191,19 +237,82 @@ static hipError_t io_address(double** p) {
   return e == hipSuccess && a == nullptr ? hipErrorInvalidSymbol : e;
 }
 
-// One model of a handle: its state block and the shape of its canonical block.
-struct Model {
-  void* st;
+// A part of a handle's canonical state: a model's block, or the fused bits or the counters of List 1.
+struct Part {
+  enum Kind { kModel, kBits, kCounters } kind;
+  uint64_t count;  // elements
+  void* st;        // a model's state block and the rest of it
   uint32_t C;
   const ModelConsts* k;
   const uint8_t* flags;  // the pixels' hole counts (depth), or none
+  BlockMap map;
 };
+constexpr int kMaxParts = 4;
 
-static int models_of(const gmm_handle* h, Model (&m)[2]) {
-  int n = 0;
-  if (has_rgb(h)) m[n++] = Model{h->st_rgb, is_augmented(h) ? 4u : 3u, &h->kc, nullptr};
-  if (sep_depth(h)) m[n++] = Model{h->st_depth, 1u, &h->kd, h->fstate};
-  return n;
+// The parts of a handle's canonical state, in its order.
+static int parts_of(const gmm_handle* h, Part (&p)[kMaxParts]) {
+  const uint64_t n = static_cast<uint64_t>(h->npix), M = static_cast<uint64_t>(h->cfg.M);
+  int c = 0;
+  const auto model = [&](void* st, uint32_t C, const ModelConsts& k, const uint8_t* flags) {
+    p[c++] = Part{Part::kModel, (C + 2) * M * n, st, C, &k, flags, block_map(h, C, k)};
+  };
+  if (has_rgb(h)) model(h->st_rgb, is_augmented(h) ? 4u : 3u, h->kc, nullptr);
+  if (sep_depth(h)) model(h->st_depth, 1u, h->kd, h->fstate);
+  if (sep_both(h)) {
+    p[c++] = Part{Part::kBits, n, nullptr, 0, nullptr, nullptr, {}};
+    p[c++] = Part{Part::kCounters, n, nullptr, 0, nullptr, nullptr, {}};
+  }
+  return c;
+}
+
+static uint64_t elements_of(const Part* p, int n) {
+  uint64_t total = 0;
+  for (int i = 0; i < n; ++i) total += p[i].count;
+  return total;
+}
+
+// Elements [e0, e0 + count) of a part into `out`.
+static hipError_t unpack_part(const gmm_handle* h, const Part& p, double* out, uint32_t e0, uint32_t count, hipStream_t s) {
+  if (p.kind == Part::kModel) {
+    switch (h->cfg.state_dtype) {
+      case GMM_F32: return launch_unpack<float>(p.st, p.flags, p.map, out, e0, count, s);
+      case GMM_F16: return launch_unpack<f16s>(p.st, p.flags, p.map, out, e0, count, s);
+      default: return launch_unpack<bf16s>(p.st, p.flags, p.map, out, e0, count, s);
+    }
+  }
+  if (p.kind == Part::kBits)
+    unpack_fuse_kernel<true><<<blocks_for(count), dim3(kBlock), 0, s>>>(h->fstate, out, e0, count);
+  else
+    unpack_fuse_kernel<false><<<blocks_for(count), dim3(kBlock), 0, s>>>(h->fstate, out, e0, count);
+  return hipGetLastError();
+}
+
+static hipError_t pack_part(const gmm_handle* h, const Part& p, const double* in, uint32_t e0, uint32_t count, hipStream_t s) {
+  if (p.kind == Part::kModel) {
+    switch (h->cfg.state_dtype) {
+      case GMM_F32: return launch_pack<float>(p.st, p.map, in, e0, count, s);
+      case GMM_F16: return launch_pack<f16s>(p.st, p.map, in, e0, count, s);
+      default: return launch_pack<bf16s>(p.st, p.map, in, e0, count, s);
+    }
+  }
+  if (p.kind == Part::kBits)
+    pack_fuse_kernel<true><<<blocks_for(count), dim3(kBlock), 0, s>>>(h->fstate, in, e0, count);
+  else
+    pack_fuse_kernel<false><<<blocks_for(count), dim3(kBlock), 0, s>>>(h->fstate, in, e0, count);
+  return hipGetLastError();
+}
+
+// fn(part, first element in the part, element in the piece, count) for every part that elements
+// [e0, e0 + count) of the canonical state touch; stops at the first error.
+template <typename F>
+static hipError_t each_part(const Part* p, int n, uint64_t e0, uint64_t count, F fn) {
+  hipError_t e = hipSuccess;
+  uint64_t at = 0;
+  for (int i = 0; i < n && e == hipSuccess; at += p[i].count, ++i) {
+    const uint64_t a = std::max(at, e0), b = std::min(at + p[i].count, e0 + count);
+    if (a < b) e = fn(p[i], static_cast<uint32_t>(a - at), static_cast<size_t>(a - e0), static_cast<uint32_t>(b - a));
+  }
+  return e;
 }
 
 }  // namespace rgbd
@@ -219,36 +328,20 @@ gmm_status gmm_read_state(gmm_handle* h, double* host_out, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "state copy to host");
-  std::lock_guard<std::mutex> lk(g_io_mu[h->cfg.device % kLocks]);
   double* buf = nullptr;
   e = io_address(&buf);
   if (e != hipSuccess) return hip_fail(e, "address of the state I/O buffer");
-  const uint32_t n = static_cast<uint32_t>(h->npix), M = static_cast<uint32_t>(h->cfg.M);
-  double* o = host_out;
-  Model models[2];
-  const int nm = models_of(h, models);
-  for (int i = 0; i < nm; ++i) {
-    const Model& m = models[i];
-    const BlockMap b = block_map(h, m.C, *m.k);
-    const uint32_t total = (m.C + 2) * M * n;  // < 2^32: the block's bytes are below 2^31
-    for (uint32_t e0 = 0; e0 < total && e == hipSuccess; e0 += kChunk) {
-      const uint32_t count = std::min(kChunk, total - e0);
-      switch (h->cfg.state_dtype) {
-        case GMM_F32: e = launch_unpack<float>(m.st, m.flags, b, buf, e0, count, s); break;
-        case GMM_F16: e = launch_unpack<f16s>(m.st, m.flags, b, buf, e0, count, s); break;
-        default: e = launch_unpack<bf16s>(m.st, m.flags, b, buf, e0, count, s); break;
-      }
-      if (e == hipSuccess) e = hipMemcpyAsync(o + e0, buf, sizeof(double) * count, hipMemcpyDeviceToHost, s);
-    }
-    o += total;
-  }
-  if (sep_both(h)) {
-    for (uint32_t e0 = 0; e0 < 2 * n && e == hipSuccess; e0 += kChunk) {
-      const uint32_t count = std::min(kChunk, 2 * n - e0);
-      unpack_fuse_kernel<<<blocks_for(count), dim3(kBlock), 0, s>>>(h->fstate, n, buf, e0, count);
-      e = hipGetLastError();
-      if (e == hipSuccess) e = hipMemcpyAsync(o + e0, buf, sizeof(double) * count, hipMemcpyDeviceToHost, s);
-    }
+  Part parts[kMaxParts];
+  const int n = parts_of(h, parts);
+  const uint64_t total = elements_of(parts, n);
+  const IoSegments io(h->cfg.device, total);
+  buf = io.in(buf);
+  for (uint64_t e0 = 0; e0 < total && e == hipSuccess; e0 += io.elements()) {
+    const uint64_t count = std::min<uint64_t>(io.elements(), total - e0);
+    e = each_part(parts, n, e0, count, [&](const Part& p, uint32_t at, size_t to, uint32_t c) {
+      return unpack_part(h, p, buf + to, at, c, s);
+    });
+    if (e == hipSuccess) e = hipMemcpyAsync(host_out + e0, buf, sizeof(double) * count, hipMemcpyDeviceToHost, s);
   }
   const hipError_t es = hipStreamSynchronize(s);  // on an error too: nothing may still use the buffer
   if (e == hipSuccess) e = es;
@@ -258,16 +351,15 @@ gmm_status gmm_read_state(gmm_handle* h, double* host_out, void* stream) {
 
 gmm_status gmm_write_state(gmm_handle* h, const double* host_in, void* stream) {
   if (!h || !host_in) return fail(GMM_ERR_INVALID_ARG, "NULL argument");
-  const uint32_t n = static_cast<uint32_t>(h->npix), M = static_cast<uint32_t>(h->cfg.M);
-  Model models[2];
-  const int nm = models_of(h, models);
-  size_t params = 0;
-  for (int i = 0; i < nm; ++i) params += static_cast<size_t>(models[i].C + 2) * M * n;
-  const double* fuse_in = host_in + params;
+  Part parts[kMaxParts];
+  const int n = parts_of(h, parts);
+  const uint64_t total = elements_of(parts, n);
   if (sep_both(h)) {  // no early exit and no call: the loop vectorises
+    const size_t npix = static_cast<size_t>(h->npix);
+    const double* fuse_in = host_in + (total - 2 * npix);
     int bad_bit = 0, bad_count = 0;
-    for (uint32_t i = 0; i < n; ++i) {
-      const double I = fuse_in[i], c = fuse_in[static_cast<size_t>(n) + i];
+    for (size_t i = 0; i < npix; ++i) {
+      const double I = fuse_in[i], c = fuse_in[npix + i];
       const double r = c >= -3.0 && c <= 3.0 ? c : 0.5;  // 0.5: not an integer
       bad_bit |= !(I == 0.0 || I == 1.0);
       bad_count |= r != static_cast<double>(static_cast<int>(r));
@@ -280,46 +372,30 @@ gmm_status gmm_write_state(gmm_handle* h, const double* host_in, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "state copy to device");
-  std::lock_guard<std::mutex> lk(g_io_mu[h->cfg.device % kLocks]);
   double* buf = nullptr;
   e = io_address(&buf);
   if (e != hipSuccess) return hip_fail(e, "address of the state I/O buffer");
-  const double* in = host_in;
-  for (int i = 0; i < nm; ++i) {
-    const Model& m = models[i];
-    const BlockMap b = block_map(h, m.C, *m.k);
-    const uint32_t total = (m.C + 2) * M * n;
-    for (uint32_t e0 = 0; e0 < total && e == hipSuccess; e0 += kChunk) {
-      const uint32_t count = std::min(kChunk, total - e0);
-      e = hipMemcpyAsync(buf, in + e0, sizeof(double) * count, hipMemcpyHostToDevice, s);
-      if (e != hipSuccess) break;
-      switch (h->cfg.state_dtype) {
-        case GMM_F32: e = launch_pack<float>(m.st, b, buf, e0, count, s); break;
-        case GMM_F16: e = launch_pack<f16s>(m.st, b, buf, e0, count, s); break;
-        default: e = launch_pack<bf16s>(m.st, b, buf, e0, count, s); break;
-      }
-    }
-    in += total;
-    if (e == hipSuccess && scaled_weights(static_cast<uint32_t>(h->esize))) {  // the weights as written: scale 1
-      unit_scale_kernel<<<blocks_for(h->tiles64), dim3(kBlock), 0, s>>>(
-          reinterpret_cast<float*>(static_cast<uint8_t*>(m.st) + b.scale), h->tiles64);
-      e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = launch_rekey(m.st, h->cfg.state_dtype, h->tiles64, h->cfg.M, static_cast<int>(m.C), s);
+  const IoSegments io(h->cfg.device, total);
+  buf = io.in(buf);
+  // no holes counted; List 1 state, where there is one, with the elements below
+  if (sep_depth(h)) e = launch_fill_u8(h->fstate, kFuseInit, static_cast<int64_t>(h->fuse_bytes), s);
+  for (uint64_t e0 = 0; e0 < total && e == hipSuccess; e0 += io.elements()) {
+    const uint64_t count = std::min<uint64_t>(io.elements(), total - e0);
+    e = hipMemcpyAsync(buf, host_in + e0, sizeof(double) * count, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+      e = each_part(parts, n, e0, count, [&](const Part& p, uint32_t at, size_t from, uint32_t c) {
+        return pack_part(h, p, buf + from, at, c, s);
+      });
   }
-  // the flags: List 1 state where there is one, no holes counted
-  if (e == hipSuccess && sep_depth(h)) e = launch_fill_u8(h->fstate, kFuseInit, static_cast<int64_t>(h->fuse_bytes), s);
-  if (sep_both(h)) {
-    constexpr uint32_t half = kChunk / 2;
-    for (uint32_t p0 = 0; p0 < n && e == hipSuccess; p0 += half) {
-      const uint32_t count = std::min(half, n - p0);
-      e = hipMemcpyAsync(buf, fuse_in + p0, sizeof(double) * count, hipMemcpyHostToDevice, s);
-      if (e == hipSuccess)
-        e = hipMemcpyAsync(buf + count, fuse_in + static_cast<size_t>(n) + p0, sizeof(double) * count, hipMemcpyHostToDevice, s);
-      if (e != hipSuccess) break;
-      pack_fuse_kernel<<<blocks_for(count), dim3(kBlock), 0, s>>>(h->fstate + p0, buf, count);
+  for (int i = 0; i < n && e == hipSuccess; ++i) {
+    const Part& p = parts[i];
+    if (p.kind != Part::kModel) continue;
+    if (scaled_weights(static_cast<uint32_t>(h->esize))) {  // the weights as written: scale 1
+      unit_scale_kernel<<<blocks_for(h->tiles64), dim3(kBlock), 0, s>>>(
+          reinterpret_cast<float*>(static_cast<uint8_t*>(p.st) + p.map.scale), h->tiles64);
       e = hipGetLastError();
     }
+    if (e == hipSuccess) e = launch_rekey(p.st, h->cfg.state_dtype, h->tiles64, h->cfg.M, static_cast<int>(p.C), s);
   }
   const hipError_t es = hipStreamSynchronize(s);  // on an error too: nothing may still use the buffer
   if (e == hipSuccess) e = es;

@@ -6,6 +6,9 @@
 #include <cxxabi.h>
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
+#include <chrono>
+#include <condition_variable>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -14,6 +17,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "gmm.h"
@@ -37,6 +41,8 @@ struct Runtime {
   std::map<uintptr_t, Region> regions;
   std::vector<Launch> launches;
   size_t h2d = 0, d2h = 0;  // asynchronous copies
+  std::function<void(const void* dst, const void* src, size_t n)> on_copy;  // called by them, unlocked
+  std::function<void()> on_sync;                                            // and by stream synchronisations
 };
 static Runtime& rt() {
   static Runtime r;
@@ -126,7 +132,8 @@ hipError_t hipFree(void* p) { return release(p); }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) { return allocate(p, n, hipMemoryTypeHost, flags); }
 hipError_t hipHostFree(void* p) { return release(p); }
 hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
-hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind kind, hipStream_t) {
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind kind, hipStream_t) {
+  if (rt().on_copy) rt().on_copy(dst, src, n);
   std::lock_guard<std::mutex> lk(rt().mu);
   (kind == hipMemcpyHostToDevice ? rt().h2d : rt().d2h) += kind == hipMemcpyDeviceToDevice ? 0 : 1;
   return hipSuccess;
@@ -161,7 +168,10 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.f, hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return *s = reinterpret_cast<hipStream_t>(1), hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) {
+  if (rt().on_sync) rt().on_sync();
+  return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 
 }  // extern "C"
@@ -504,6 +514,85 @@ static void cache_policy() {
   for (auto* g : h) OK(gmm_destroy(g));
 }
 
+// Reads and writes of states on one device run side by side, each in memory of its own.
+static void state_io() {
+  std::mutex mu;
+  std::condition_variable cv;
+  constexpr int kCalls = 24;
+  const int sizes[][2] = {{64, 48}, {160, 120}, {320, 240}, {17, 13}};
+  std::vector<gmm_handle*> h;
+  std::vector<std::vector<double>> host(kCalls);
+  for (int i = 0; i < kCalls; ++i) {
+    h.push_back(handle(sizes[i % 4][0], sizes[i % 4][1], GMM_RGB | GMM_DEPTH, 5, i % 2 ? GMM_F16 : GMM_F32));
+    size_t n = 0;
+    OK(gmm_state_size(h[i], &n));
+    host[i].assign(n, 0.0);
+  }
+  // a call whose copy takes its time does not hold up another one
+  bool open = false, done = false;
+  std::thread::id slow;
+  rt().on_copy = [&](const void*, const void*, size_t) {
+    std::unique_lock<std::mutex> lk(mu);
+    if (std::this_thread::get_id() == slow) cv.wait(lk, [&] { return open; });
+  };
+  std::thread a([&] {
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      slow = std::this_thread::get_id();
+    }
+    cv.notify_all();
+    OK(gmm_read_state(h[2], host[2].data(), nullptr));
+  });
+  std::this_thread::sleep_for(std::chrono::milliseconds(50));
+  std::thread b([&] {
+    OK(gmm_write_state(h[0], host[0].data(), nullptr));
+    OK(gmm_read_state(h[0], host[0].data(), nullptr));
+    std::lock_guard<std::mutex> lk(mu);
+    done = true;
+    cv.notify_all();
+  });
+  {
+    std::unique_lock<std::mutex> lk(mu);
+    EXPECT(cv.wait_for(lk, std::chrono::seconds(5), [&] { return done; }));
+    open = true;
+  }
+  cv.notify_all();
+  a.join();
+  b.join();
+  // what calls at the same time copy from and to the device never overlaps, until they have drained
+  std::map<std::thread::id, std::pair<const char*, const char*>> busy;
+  int overlaps = 0, most = 0;
+  rt().on_copy = [&](const void* dst, const void* src, size_t n) {
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      const bool read = std::any_of(host.begin(), host.end(), [&](const std::vector<double>& v) {
+        return dst >= v.data() && dst < v.data() + v.size();
+      });
+      const char* p = static_cast<const char*>(read ? src : dst);
+      for (const auto& o : busy) overlaps += o.first != std::this_thread::get_id() && p < o.second.second && o.second.first < p + n;
+      busy[std::this_thread::get_id()] = {p, p + n};
+      most = std::max(most, static_cast<int>(busy.size()));
+    }
+    std::this_thread::sleep_for(std::chrono::milliseconds(2));
+  };
+  rt().on_sync = [&] {
+    std::lock_guard<std::mutex> lk(mu);
+    busy.erase(std::this_thread::get_id());
+  };
+  std::vector<std::thread> calls;
+  for (int i = 0; i < kCalls; ++i)
+    calls.emplace_back([&, i] {
+      OK(gmm_read_state(h[i], host[i].data(), nullptr));
+      OK(gmm_write_state(h[i], host[i].data(), nullptr));
+    });
+  for (auto& t : calls) t.join();
+  EXPECT(overlaps == 0);
+  EXPECT(most > 4);
+  rt().on_copy = nullptr;
+  rt().on_sync = nullptr;
+  for (auto* g : h) OK(gmm_destroy(g));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
@@ -514,6 +603,7 @@ int main(int argc, char** argv) {
       {"exec_tuning", exec_tuning},
       {"residency", residency},
       {"cache_policy", cache_policy},
+      {"state_io", state_io},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);
