@@ -19,6 +19,7 @@
 #include <set>
 #include <sstream>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "gmm.h"
@@ -220,6 +221,12 @@ static gmm_status validate_tuning(const gmm_batch_tuning* t) {
     return fail(GMM_ERR_INVALID_ARG, "tile_pixels must be a multiple of block_threads, at most 64x it");
   if (t->blocks_per_cu < 1 || t->blocks_per_cu > 32) return fail(GMM_ERR_INVALID_ARG, "blocks_per_cu must be in 1..32");
   return GMM_OK;
+}
+
+static uint32_t count_tiles(const gmm_batch* b, uint32_t tile_px) {
+  uint64_t total = 0;
+  for (const auto* h : b->handles) total += (static_cast<uint64_t>(h->npix) + tile_px - 1) / tile_px;
+  return static_cast<uint32_t>(std::min<uint64_t>(total, UINT32_MAX));
 }
 
 // First tiles for tile size `tile_px` (synchronous; not for use under capture).
@@ -502,10 +509,15 @@ gmm_status gmm_batch_autotune(gmm_batch* b, int32_t slot, void* stream, gmm_batc
     const int blocks[] = {256, 512};
     const int tile_mult[] = {1, 2, 4, 8, 16};
     const int per_cu[] = {2, 4, 8, 16};
+    // candidates often come to the same launch (with 2048 threads a CU or more, one block per tile):
+    // each launch is tried once, by threads, pixels per piece and blocks
+    std::set<std::tuple<int, uint32_t, uint32_t>> tried;
     for (int bt : blocks) {
       for (int tm : tile_mult) {
         for (int pc : per_cu) {
           gmm_batch_tuning t{bt, bt * tm, pc};
+          const BatchLaunch l = batch_launch(t, count_tiles(b, static_cast<uint32_t>(t.tile_pixels)), b->pixels, b->cu_count);
+          if (!tried.insert({l.block, l.tile_px >> l.piece_shift, l.grid}).second) continue;
           st = apply_tuning(b, t);
           if (st != GMM_OK) break;
           e = run_slot(b, slot, hs);  // warm-up

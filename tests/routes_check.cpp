@@ -593,6 +593,37 @@ static void state_io() {
   for (auto* g : h) OK(gmm_destroy(g));
 }
 
+// The autotuner times every launch once: candidates that come to the same blocks on the same pixels
+// are one.
+static void autotune() {
+  void* mem = nullptr;
+  (void)hipMalloc(&mem, 1 << 23);
+  uint8_t* d = static_cast<uint8_t*>(mem);
+  uint64_t* m = reinterpret_cast<uint64_t*>(mem);
+  const auto trials = [&](int w, int h, int n) {
+    std::vector<gmm_handle*> g;
+    for (int i = 0; i < n; ++i) g.push_back(handle(w, h));
+    const std::vector<gmm_stream_io> io(n, {d, 3 * w, reinterpret_cast<uint16_t*>(d), 2 * w, m, m, nullptr});
+    gmm_batch* b = nullptr;
+    OK(gmm_batch_create(g.data(), n, 1, &b));
+    OK(gmm_batch_set_frames(b, 0, io.data(), nullptr));
+    const size_t before = rt().launches.size();
+    gmm_batch_tuning best{};
+    OK(gmm_batch_autotune(b, 0, nullptr, &best, nullptr));
+    const size_t made = rt().launches.size() - before;
+    gmm_batch_tuning now{};
+    OK(gmm_batch_get_tuning(b, &now));
+    EXPECT(std::memcmp(&now, &best, sizeof now) == 0);
+    OK(gmm_batch_destroy(b));
+    for (auto* x : g) OK(gmm_destroy(x));
+    return made / 2;  // a warm-up and a timed launch each
+  };
+  // 256 threads: 2 or 4 blocks a CU walk, more are a block per tile; 512: 2 walk. Five tile sizes each.
+  EXPECT(trials(1920, 1080, 16) == 15 + 10);
+  // so few pixels that every tile has a block whatever the blocks per CU: the five tile sizes are left
+  EXPECT(trials(64, 64, 2) == 5 + 5);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
@@ -604,6 +635,7 @@ int main(int argc, char** argv) {
       {"residency", residency},
       {"cache_policy", cache_policy},
       {"state_io", state_io},
+      {"autotune", autotune},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);
