@@ -199,7 +199,7 @@ struct gmm_batch {
   std::vector<gmm_handle*> handles;
   int n_slots = 0;
   FrameArgs* d_table = nullptr;              // n_slots x n descriptors
-  std::vector<FrameArgs*> h_staging;         // pinned, one per slot
+  std::vector<FrameArgs*> h_staging;         // pinned, one per slot (n > kPackStreams)
   std::vector<hipEvent_t> staging_done;      // last upload from each staging buffer
   std::vector<uint8_t> slot_ready;
   std::vector<uint8_t> slot_measure;         // a stream of the slot's descriptors has a traffic record
@@ -333,11 +333,12 @@ gmm_status gmm_batch_create(gmm_handle* const* handles, int32_t n, int32_t n_slo
     free_batch(b);
     return fail(GMM_ERR_OUT_OF_MEMORY, "device allocation of the batch tables failed");
   }
-  b->h_staging.assign(n_slots, nullptr);
-  b->staging_done.assign(n_slots, nullptr);
+  const bool pack = n_streams(b) <= kPackStreams;
+  b->h_staging.assign(pack ? 0 : n_slots, nullptr);
+  b->staging_done.assign(pack ? 0 : n_slots, nullptr);
   b->slot_ready.assign(n_slots, 0);
   b->slot_measure.assign(n_slots, 0);
-  for (int32_t s = 0; s < n_slots; ++s) {
+  for (size_t s = 0; s < b->h_staging.size(); ++s) {
     e = hipHostMalloc(reinterpret_cast<void**>(&b->h_staging[s]), static_cast<size_t>(n) * sizeof(FrameArgs),
                       hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->staging_done[s], hipEventDisableTiming);
@@ -407,7 +408,8 @@ gmm_status gmm_batch_set_frames(gmm_batch* b, int32_t slot, const gmm_stream_io*
   const bool pack = n_streams(b) <= kPackStreams;
   hipError_t e = pack ? hipSuccess : hipEventSynchronize(b->staging_done[slot]);  // previous upload from this buffer
   if (e != hipSuccess) return hip_fail(e, "staging event");
-  FrameArgs* host = b->h_staging[slot];
+  FrameArgs packed[kPackStreams];
+  FrameArgs* host = pack ? packed : b->h_staging[slot];
   bool measure = false;
   for (size_t i = 0; i < n_streams(b); ++i) {
     const gmm_stream_io& s = io[i];

@@ -205,6 +205,12 @@ struct Counts {
   size_t h2d, d2h;
 };
 
+static size_t host_allocations() {
+  size_t n = 0;
+  for (const auto& r : rt().regions) n += r.second.type == hipMemoryTypeHost;
+  return n;
+}
+
 // One tick of an executor, waited for: the copies of frames and masks it made.
 static Counts tick(gmm_exec* x, const std::vector<gmm_exec_item>& items) {
   const Counts before{rt().h2d, rt().d2h};
@@ -624,6 +630,30 @@ static void autotune() {
   EXPECT(trials(64, 64, 2) == 5 + 5);
 }
 
+// A batch has page-locked staging memory only where descriptors are copied from it: above 32 streams.
+static void staging() {
+  std::vector<gmm_handle*> h;
+  for (int i = 0; i < 33; ++i) h.push_back(handle(64, 48, GMM_RGB));
+  for (int n : {1, 32, 33}) {
+    const size_t before = host_allocations();
+    gmm_batch* b = nullptr;
+    OK(gmm_batch_create(h.data(), n, 3, &b));
+    EXPECT(host_allocations() - before == (n > 32 ? 3u : 0u));
+    void* mem = nullptr;
+    (void)hipMalloc(&mem, 1 << 16);
+    const std::vector<gmm_stream_io> io(n, {static_cast<uint8_t*>(mem), 3 * 64, nullptr, 0, static_cast<uint64_t*>(mem), nullptr, nullptr});
+    const size_t copies = rt().h2d;
+    for (int slot = 0; slot < 3; ++slot) {
+      OK(gmm_batch_set_frames(b, slot, io.data(), nullptr));
+      OK(gmm_batch_run(b, slot, nullptr));
+    }
+    EXPECT(rt().h2d - copies == (n > 32 ? 3u : 0u));
+    OK(gmm_batch_destroy(b));
+    EXPECT(host_allocations() == before);
+  }
+  for (auto* g : h) OK(gmm_destroy(g));
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void()>> checks = {
       {"gap", gap},
@@ -636,6 +666,7 @@ int main(int argc, char** argv) {
       {"cache_policy", cache_policy},
       {"state_io", state_io},
       {"autotune", autotune},
+      {"staging", staging},
   };
   for (int i = 1; i < argc; ++i) {
     const auto it = checks.find(argv[i]);

@@ -28,7 +28,7 @@ def exe(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["gap", "coherence", "overlap", "detach", "round_trip", "exec_tuning", "residency",
-                                   "cache_policy", "state_io", "autotune"])
+                                   "cache_policy", "state_io", "autotune", "staging"])
 def test_routes(exe, check):
     r = subprocess.run([exe, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "routes ok" in r.stdout, r.stdout + r.stderr
