@@ -502,6 +502,28 @@ static void cache_policy() {
     EXPECT(batches(2, 8, fixed) == 0);
     EXPECT(batches(4, 8, fixed) == 2);
   }
+  // a frame of a stream larger than the cache, between two frames of a small one, makes the small one's
+  // rows stream, in every state type and by every call
+  gmm_handle* big = handle(3072, 2048);
+  for (int dtype : {GMM_F32, GMM_F16, GMM_BF16}) {
+    std::vector<gmm_handle*> g;
+    for (int i = 0; i < 6; ++i) g.push_back(handle(64, 48, GMM_RGB | GMM_DEPTH, 5, dtype));
+    const std::vector<gmm_stream_io> small(6, {d, 3 * 64, reinterpret_cast<uint16_t*>(d), 2 * 64, m, m + 48, nullptr});
+    const std::vector<std::function<void()>> calls = {
+        [&] { OK(gmm_apply_frame(g[0], d, 192, reinterpret_cast<uint16_t*>(d), 128, m, m + 48, nullptr)); },
+        [&] { OK(gmm_batch_apply_static(g.data(), 6, small.data(), nullptr, nullptr)); }};
+    for (const auto& call : calls) {
+      call();
+      call();
+      EXPECT(policy() == 0);
+      OK(gmm_apply_frame(big, d, 3 * 3072, reinterpret_cast<uint16_t*>(d), 2 * 3072, m, m, nullptr));
+      EXPECT(policy() == 2);
+      call();
+      EXPECT(policy() == 2);
+    }
+    for (auto* q : g) OK(gmm_destroy(q));
+  }
+  OK(gmm_destroy(big));
   // two executors, 12 streams each, each stream in turn; then one stream of them alone
   gmm_exec* x[2] = {};
   for (auto& e : x) OK(gmm_exec_create(0, 2, &e));
