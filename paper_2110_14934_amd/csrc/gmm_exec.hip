@@ -234,7 +234,11 @@ static bool masks_apart(std::vector<Buffer>& b) {
 // Two blocks of 256 threads read as fast (16 VGA fp16 streams 503 us a tick, 516 with full CUs; 12 fp32
 // streams 395 and 398; all pixels changing 535 and 577) and leave the batch at 138 us, the product at
 // 223. One block is slower where fp32 rows move (405 us for the 12 streams), three let 450 us pass.
+// A tick over in some 100 us has no time to read at full rate anyway, and more blocks start it faster:
+// 3 VGA fp16 streams (0.9 M pixels) 117 us with two blocks a CU and 113 with full ones, 4 streams (1.2 M)
+// 143 and 141 to 145, 6 streams 200 and 207.
 constexpr uint32_t kLinkBlocksPerCu = 2;
+constexpr uint64_t kShortTickPixels = uint64_t(1) << 20;
 
 static size_t mask_bytes(const gmm_handle* h) { return static_cast<size_t>((h->npix + 63) / 64) * 8; }
 
@@ -510,8 +514,8 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
   }
   if (e == hipSuccess) {
     BatchLaunch l = batch_launch(tun, static_cast<uint32_t>(total_tiles), pixels, x->cu_count);
-    if (linked && (walks(tun) || is_open(tun)))
-      limit_residency(l, is_open(tun) ? kLinkBlocksPerCu : static_cast<uint32_t>(tun.blocks_per_cu));
+    if (linked && walks(tun)) limit_residency(l, static_cast<uint32_t>(tun.blocks_per_cu));
+    if (linked && is_open(tun) && pixels >= kShortTickPixels) limit_residency(l, kLinkBlocksPerCu);
     l.n_streams = static_cast<uint32_t>(n);
     l.measure = measure;
     l.stream = streams_rows(s.handles.data(), s.handles.size());
