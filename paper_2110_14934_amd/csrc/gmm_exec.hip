@@ -21,7 +21,6 @@
 #include <condition_variable>
 #include <cstring>
 #include <deque>
-#include <functional>
 #include <map>
 #include <mutex>
 #include <new>
@@ -207,38 +206,57 @@ static void* in_place(const void* p, size_t bytes, size_t align, int device) {
   return at <= size && bytes <= size - at ? a.devicePointer : nullptr;
 }
 
-// Host memory of a tick: a frame that the kernel reads in place, or a mask.
+// A buffer of a tick in host memory.
 struct Buffer {
-  const void *begin, *end;
-  bool mask;
+  uintptr_t begin, end;
 };
 
+static Buffer buffer(const void* p, size_t bytes) {
+  return Buffer{reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + bytes};
+}
+
 // Whether every mask is apart from every other mask and from the frames read in place (frames may
-// share memory). Reorders `b`.
-static bool masks_apart(std::vector<Buffer>& b) {
-  const std::less<const void*> before;
-  std::sort(b.begin(), b.end(), [&](const Buffer& x, const Buffer& y) { return before(x.begin, y.begin); });
-  const void *end = nullptr, *mask_end = nullptr;  // of the buffers and of the masks so far
-  for (const Buffer& x : b) {
-    if (before(x.begin, x.mask ? end : mask_end)) return false;
-    if (before(end, x.end)) end = x.end;
-    if (x.mask && before(mask_end, x.end)) mask_end = x.end;
+// share memory). Sorts them where it has to: masks that lie in ascending order, away from all frames,
+// as a server's do, cost a pass.
+static bool masks_apart(std::vector<Buffer>& masks, std::vector<Buffer>& frames) {
+  const auto by_begin = [](const Buffer& x, const Buffer& y) { return x.begin < y.begin; };
+  if (!std::is_sorted(masks.begin(), masks.end(), by_begin)) std::sort(masks.begin(), masks.end(), by_begin);
+  for (size_t i = 1; i < masks.size(); ++i)
+    if (masks[i].begin < masks[i - 1].end) return false;
+  if (masks.empty()) return true;
+  const uintptr_t first = masks.front().begin, last = masks.back().end;
+  frames.erase(std::remove_if(frames.begin(), frames.end(), [&](const Buffer& f) { return f.end <= first || f.begin >= last; }),
+               frames.end());
+  std::sort(frames.begin(), frames.end(), by_begin);
+  size_t m = 0;  // masks before it end at or before the frame's begin
+  for (const Buffer& f : frames) {
+    while (m < masks.size() && masks[m].end <= f.begin) ++m;
+    if (m < masks.size() && masks[m].begin < f.end) return false;
   }
   return true;
 }
 
-// Blocks that a tick reading frames in place keeps on a CU, with the default shape. Such a tick lasts as
-// long as its frames take over the link (500 us for 16 VGA streams, of which the kernel would need 85),
-// and blocks that filled the CUs all that time kept other work off the device: a batch of 16 VGA fp32
-// streams, 90 us alone, took 620 us beside ticks, a 4096 bf16 matrix product 615 us instead of 134.
-// Two blocks of 256 threads read as fast (16 VGA fp16 streams 503 us a tick, 516 with full CUs; 12 fp32
-// streams 395 and 398; all pixels changing 535 and 577) and leave the batch at 138 us, the product at
-// 223. One block is slower where fp32 rows move (405 us for the 12 streams), three let 450 us pass.
+// The default shape of a tick that reads frames in place. Such a tick lasts as long as its frames take
+// over the link (500 us for 16 VGA streams, of which the kernel would need 85), and blocks that fill the
+// CUs all that time keep other work off the device: a batch of 16 VGA fp32 streams, 90 us alone, takes
+// 630 us beside such ticks, a 4096 bf16 matrix product 627 us instead of 134. Two blocks a CU read paired
+// frames, or depth, as fast and leave them at 138 and 223 us (ticks of 16 VGA fp16 streams 523 us with
+// full CUs and 511 with two blocks, 24 fp32 ones 765 and 757, 8 of 1920x1080 fp32 1564 and 1570, 24 depth
+// streams of 512x424 240 and 225). Where most bytes are colour alone (3 to 4 bytes a pixel), two blocks
+// are slower: 16 VGA colour streams 305 and 316 us, 16 streams of four kinds 543 and 566; such ticks keep
+// full CUs. One block is faster still in most cases, but the LDS it takes to hold the others off leaves no
+// room beside kernels that use much of it themselves (a tick beside matrix products 1910 us; 549 with
+// two blocks, 522 with full CUs). Waves that stay and take pieces by tickets, with no LDS held, read 20 %
+// slower (16 VGA fp16 streams 620 us): the order in which the dispatcher hands out blocks keeps what is
+// on its way together.
 // A tick over in some 100 us has no time to read at full rate anyway, and more blocks start it faster:
-// 3 VGA fp16 streams (0.9 M pixels) 117 us with two blocks a CU and 113 with full ones, 4 streams (1.2 M)
-// 143 and 141 to 145, 6 streams 200 and 207.
-constexpr uint32_t kLinkBlocksPerCu = 2;
+// 3 VGA fp16 streams (0.9 M pixels) 117 us with two blocks a CU and 113 with full ones.
 constexpr uint64_t kShortTickPixels = uint64_t(1) << 20;
+constexpr uint32_t kLinkBlocksPerCu = 2;
+
+static bool leaves_room(uint64_t pixels, uint64_t frame_bytes) {
+  return pixels >= kShortTickPixels && (frame_bytes < 3 * pixels || frame_bytes >= 4 * pixels);
+}
 
 static size_t mask_bytes(const gmm_handle* h) { return static_cast<size_t>((h->npix + 63) / 64) * 8; }
 
@@ -412,8 +430,9 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     size_t off[3];       // offset in the arena, or SIZE_MAX
   };
   std::vector<Place> place(n);
-  std::vector<Buffer> used;
-  used.reserve(5 * static_cast<size_t>(n));
+  std::vector<Buffer> frames, masks;
+  frames.reserve(2 * static_cast<size_t>(n));
+  masks.reserve(3 * static_cast<size_t>(n));
   size_t mask_total = 0;
   bool linked = false;  // some frame is read in place
   for (int32_t i = 0; i < n; ++i) {
@@ -424,17 +443,17 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     p.rgb = static_cast<const uint8_t*>(in_place(it.host_rgb, px * 3, 4, x->device));
     p.depth = static_cast<const uint16_t*>(in_place(it.host_depth, px * 2, 2, x->device));
     linked = linked || p.rgb || p.depth;
-    if (p.rgb) used.push_back({it.host_rgb, it.host_rgb + px * 3, false});
-    if (p.depth) used.push_back({it.host_depth, it.host_depth + px, false});
+    if (p.rgb) frames.push_back(buffer(it.host_rgb, px * 3));
+    if (p.depth) frames.push_back(buffer(it.host_depth, px * 2));
     void* want[3] = {it.host_fg_rgb, it.host_fg_depth, it.host_fused};
     for (int m = 0; m < 3; ++m) {
       p.mask[m] = static_cast<uint64_t*>(in_place(want[m], mb, 8, x->device));
-      if (want[m]) used.push_back({want[m], static_cast<char*>(want[m]) + mb, true});
+      if (want[m]) masks.push_back(buffer(want[m], mb));
     }
   }
   // A mask over memory that the kernel reads, or over another mask, comes from the arena after the
   // kernel, and with it all masks of the tick, in the order of the items.
-  const bool apart = masks_apart(used);
+  const bool apart = masks_apart(masks, frames);
   for (int32_t i = 0; i < n; ++i) {
     const gmm_exec_item& it = items[i];
     const gmm_handle* h = it.handle;
@@ -464,7 +483,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
   const uint32_t tile_px = static_cast<uint32_t>(tun.tile_pixels);
   s.outs.clear();
   uint32_t* h_first = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s.h_table) + tab);
-  uint64_t total_tiles = 0, pixels = 0;
+  uint64_t total_tiles = 0, pixels = 0, frame_bytes = 0;
   bool measure = false;
   for (int32_t i = 0; i < n; ++i) {
     const gmm_exec_item& it = items[i];
@@ -483,6 +502,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
     h_first[i] = static_cast<uint32_t>(total_tiles);
     total_tiles += (static_cast<uint64_t>(h->npix) + tile_px - 1) / tile_px;
     pixels += static_cast<uint64_t>(h->npix);
+    frame_bytes += static_cast<uint64_t>(h->npix) * ((has_rgb(h) ? 3 : 0) + (has_depth(h) ? 2 : 0));
   }
   if (total_tiles >= (1ull << 31)) return fail(GMM_ERR_INVALID_ARG, "too many tiles in one tick");
   // copy-in of the frames not used in place, each into its stream's device slot on the least
@@ -515,7 +535,7 @@ gmm_status gmm_exec_launch(gmm_exec* x, const gmm_exec_item* items, int32_t n, u
   if (e == hipSuccess) {
     BatchLaunch l = batch_launch(tun, static_cast<uint32_t>(total_tiles), pixels, x->cu_count);
     if (linked && walks(tun)) limit_residency(l, static_cast<uint32_t>(tun.blocks_per_cu));
-    if (linked && is_open(tun) && pixels >= kShortTickPixels) limit_residency(l, kLinkBlocksPerCu);
+    if (linked && is_open(tun) && leaves_room(pixels, frame_bytes)) limit_residency(l, kLinkBlocksPerCu);
     l.n_streams = static_cast<uint32_t>(n);
     l.measure = measure;
     l.stream = streams_rows(s.handles.data(), s.handles.size());

@@ -436,31 +436,46 @@ static void exec_tuning() {
   OK(gmm_destroy(h));
 }
 
-// A tick that waits for the host link leaves most of every CU to other work: no more than two of its
-// blocks of 256 threads on a CU, and a quarter of its LDS free.
+// A tick that waits for the host link leaves most of every CU to other work: two blocks of 256 threads
+// on a CU, a quarter of its LDS free, where they keep the link busy (`blocks`: 0 where they do not).
 static void residency() {
   constexpr size_t kLdsPerCu = 160 << 10;
-  gmm_exec* x = nullptr;
-  OK(gmm_exec_create(0, 2, &x));
-  std::vector<gmm_handle*> h;
-  std::vector<gmm_exec_item> in_place, copied;
-  constexpr int W = 512, H = 128;  // 16 of them are 2^20 pixels
-  static uint8_t rgb[W * H * 3];
-  for (int i = 0; i < 40; ++i) {  // up to 32 streams' descriptors travel with the kernel, more in a table
-    h.push_back(handle(W, H, GMM_RGB));
-    OK(gmm_exec_attach(x, h.back(), nullptr));
-    in_place.push_back({h.back(), pinned(sizeof rgb), nullptr, reinterpret_cast<uint64_t*>(pinned(W * H / 8)), nullptr, nullptr});
-    copied.push_back({h.back(), rgb, nullptr, nullptr, nullptr, nullptr});
-    if (i + 1 != 1 && i + 1 != 15 && i + 1 != 16 && i + 1 != 32 && i + 1 != 40) continue;
-    (void)tick(x, in_place);
-    const Launch l = rt().launches.back();
-    if (i + 1 < 16) EXPECT(l.lds == 0);  // over before anyone waits long
-    else EXPECT(l.block == 256 && kLdsPerCu / (l.lds + 768) == 2 && kLdsPerCu - 2 * (l.lds + 768) >= kLdsPerCu / 4);
-    (void)tick(x, copied);
-    EXPECT(rt().launches.back().lds == 0);
-  }
-  OK(gmm_exec_destroy(x));
-  for (auto* g : h) OK(gmm_destroy(g));
+  const auto check = [&](int w, int h, int modalities, const std::vector<int>& counts, size_t blocks) {
+    const size_t px = static_cast<size_t>(w) * h;
+    gmm_exec* x = nullptr;
+    OK(gmm_exec_create(0, 2, &x));
+    std::vector<gmm_handle*> g;
+    std::vector<gmm_exec_item> in_place, copied;
+    std::vector<uint8_t> rgb(px * 3);
+    std::vector<uint16_t> depth(px);
+    uint8_t* p = pinned(px * 3);
+    for (int n : counts) {
+      while (static_cast<int>(g.size()) < n) {
+        g.push_back(handle(w, h, modalities));
+        OK(gmm_exec_attach(x, g.back(), nullptr));
+        const bool c = modalities & GMM_RGB, d = modalities & GMM_DEPTH;
+        in_place.push_back({g.back(), c ? p : nullptr, d ? reinterpret_cast<uint16_t*>(p) : nullptr, nullptr, nullptr, nullptr});
+        copied.push_back({g.back(), c ? rgb.data() : nullptr, d ? depth.data() : nullptr, nullptr, nullptr, nullptr});
+      }
+      (void)tick(x, in_place);
+      const Launch l = rt().launches.back();
+      const size_t fit = kLdsPerCu / (l.lds + 768);
+      const bool brief = n * px < (1 << 20);  // over before anyone waits long
+      const bool full = brief || blocks == 0;
+      if (l.block != 256 || l.grid != n * px / (brief ? 256 : 512) ||
+          (full ? l.lds != 0 : fit != blocks || kLdsPerCu - fit * (l.lds + 768) < kLdsPerCu / 4))
+        std::printf("%d of %dx%d (%d): %u blocks of %u threads, %zu bytes of LDS\n", n, w, h, modalities, l.grid, l.block, l.lds), ++g_bad;
+      (void)tick(x, copied);
+      EXPECT(rt().launches.back().lds == 0);
+    }
+    OK(gmm_exec_destroy(x));
+    for (auto* q : g) OK(gmm_destroy(q));
+  };
+  // up to 32 streams' descriptors travel with the kernel, more in a table
+  check(512, 256, GMM_RGB | GMM_DEPTH, {1, 7, 8, 32, 40}, 2);
+  check(512, 256, GMM_DEPTH, {7, 8, 40}, 2);
+  check(512, 256, GMM_RGB, {7, 8, 40}, 0);
+  check(1024, 1024, GMM_RGB | GMM_DEPTH, {1, 2}, 2);
 }
 
 // Rows are kept in the 256 MB last-level cache if they are still there when the stream's next frame
