@@ -30,8 +30,9 @@
 namespace rgbd {
 
 // Five waves per SIMD, six at M <= 3: the body fits them without spilling (checked at build time by
-// the tests; 24 small streams at M = 3 take 16.9 us with the five it would have at 82 registers,
-// 16.2 with six).
+// the tests). At M = 3 in fp32 it would have five, at 82 registers: 24 streams of 160x120 8.74 us with
+// five and 8.40 with six, 4 VGA streams 16.3 and 15.9, 96 VGA streams 410 and 394. At M = 1 and 2 and in
+// 16-bit state it has six or more anyway, and nothing changes (96 VGA streams, M = 2, fp32: 399 us).
 // A block takes one piece of a tile (tile_px >> piece_shift pixels) and the grid usually has a
 // block for every piece (batch_launch below); a smaller grid walks the pieces b, b+G, b+2G, ...
 // CP: the cache policy of the rows (kCached or kStream; streams_rows).
@@ -103,8 +104,11 @@ hipError_t launch_batch(int M, int dtype, const BatchLaunch& l, hipStream_t s) {
 // spread a block's start (the search, the descriptor) over more pixels, smaller ones leave a
 // shorter chain in each wave and an evener end. Pieces of 256 / 512 / 1024 pixels: 64 uneven fp32
 // streams (29 M pixels) 338 / 312 / 318 us, 32 VGA fp16 streams (9.8 M pixels) 145 / 140 / 147
-// us, 4 VGA fp32 streams (1.2 M) 25.1 / 23.9 / 27.1 us, 24 small fp32 streams (M = 3, 0.9 M)
-// 18.2 / 19.4 / 19.9 us, 2 fp32 streams of 320x240 (0.15 M) 8.4 / 9.6 / 13.6 us.
+// us. Where the line lies, in rows that stay in the caches: 6 VGA streams (1.8 M) M = 5 fp32 24.6 / 23.2 /
+// 24.4, fp16 21.8 / 21.9 / 23.3, M = 3 fp32 22.9 / 22.9 / 25.4; 4 VGA (1.2 M) M = 5 fp32 17.0 / 16.6 / 16.7,
+// M = 3 fp32 16.1 / 15.7 / 15.7, fp16 13.3 / 12.8 / 13.8; 3 VGA (0.9 M) M = 5 fp32 13.6 / 13.3 / 13.2, fp16 12.8 /
+// 13.3 / 13.6, M = 3 fp32 12.8 / 13.6 / 13.0; 2 of 320x240 (0.15 M) M = 5 fp32 5.0 / 6.1 / 8.8, M = 3 fp16 4.2 /
+// 5.0 / 7.0.
 constexpr uint64_t kSmallBatchPixels = uint64_t(1) << 20;
 constexpr uint32_t kMaxGrid = 1u << 22;  // blocks, so that grid x block stays below 2^32 threads
 

@@ -327,9 +327,9 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // suffix accesses and the frames could still hit. Rows that fit in the last-level cache keep the
 // default policy for loads, so that they stay there from frame to frame, and a wave whose lanes
 // all stayed on the fast path writes them through the XCD's L2 (device scope): the L2s are written
-// back at the end of a kernel in any case, and rows left dirty in them lengthen it (one VGA stream
-// 7.3 -> 6.5 us with the branch of step_store, 1920x1080 colour in fp16 16.0 -> 14.6 us, four VGA
-// streams in a batch 23.5 -> 21.3 us). A wave that also writes suffix pieces leaves both to the L2,
+// back at the end of a kernel in any case, and rows left dirty in them lengthen it (1920x1080 colour
+// in fp16 14.7 -> 13.6 us, paired in fp32 27.7 -> 26.6, four VGA fp32 streams in a batch 19.8 -> 17.8,
+// eight fp16 ones 34.3 -> 32.9; one VGA stream 6.43 us either way). A wave that also writes suffix pieces leaves both to the L2,
 // which merges the pieces: with its rows written through, a VGA clip in which most waves are such
 // waves took 10.9 instead of 10.5 us a frame, and with the pieces too a frame in which every pixel
 // writes one took a fifth longer.

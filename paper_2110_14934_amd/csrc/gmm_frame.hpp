@@ -17,10 +17,12 @@ namespace rgbd {
 // bytes. `p` must be inside the frame.
 // NT marks the frame loads non-temporal, as the rows of streaming kernels are in fp32 state: 64 uneven
 // streams, several such batches in turn, 303.5 us a launch and 310.5 without. In 16-bit state, whose
-// rows are half as many bytes, and of frames read over the link it costs more than it keeps in the
-// caches: neighbouring waves share lines of the colour frame (192 bytes each, lines of 128), which
-// are then fetched twice (32 VGA fp16 streams 135.4 us, 132.9 without; a 16-stream fp16 tick 552 and
-// 542 us).
+// rows are half as many bytes, it costs more than it keeps in the caches: neighbouring waves share
+// lines of the colour frame (192 bytes each, lines of 128), which are then fetched twice (32 VGA fp16
+// streams 135.4 us, 132.9 without; a 16-stream fp16 tick 552 and 542 us). In fp32 ticks that read
+// frames over the link it makes no difference (12 VGA streams 392 us either way, 24 streams 755 and
+// 744, less than two runs differ), nor on four-channel streams (2560x1920 66.2 us with it, 65.8
+// without), which load their frames without it.
 struct RgbLoad {
   bool staged;
   uint32_t w;           // staged: this lane's dword of the wave's bytes
@@ -113,7 +115,7 @@ __device__ __forceinline__ void load_prefix(Mix<M, C>& m, const StateBlock& blk,
 // keeps for its waits. A wave without any general-path lane skips the suffix stores, and their
 // address and packing arithmetic, by a branch the whole wave takes: they are the larger part of
 // the instructions of such a wave, and the loads the count matters for are behind them (VGA stream
-// 7.3 -> 6.8 us, 64 uneven fp32 streams 313 -> 305 us). In the direct form it skips the suffix loads
+// 6.72 -> 6.43 us, 1920x1080 paired 29.8 -> 27.7, 64 VGA fp32 streams in a batch 284 -> 278). In the direct form it skips the suffix loads
 // too (32 VGA fp16 streams 137.7 -> 135.9 us; in the scaled form the waits this costs outweigh it,
 // 306 -> 323 us).
 template <int M, int C, typename S>

@@ -18,8 +18,9 @@ __global__ void __launch_bounds__(4) clear_counts_kernel(unsigned long long* cou
   if (threadIdx.x < 4) counts[threadIdx.x] = 0ull;
 }
 
-// Set bits of (pred & truth, pred, truth): 32 bits hold a wave's (512 blocks of 16 waves reach them
-// past 2^39 words).
+// Set bits of (pred & truth, pred, truth) that one wave counts. 32 bits hold them for any mask that fits
+// a device: a mask is cut over 8192 waves, so that one reaches 2^32 bits past 2^39 words (4 TB). Sums
+// over waves take 64 bits.
 struct Ones {
   uint32_t both, pred, truth;
 };
@@ -92,12 +93,12 @@ __global__ void __launch_bounds__(kCountBlock) confusion_kernel(const uint64_t* 
   }
 }
 
-// One block, one launch up to kOneBlockWords: a VGA mask 3.4 us on the GPU and 6.7 us a call from
-// Python, where clearing and counting in many blocks takes 5.6 and 9.5 us; 10^6 pixels 5.8 and 6.7
-// against 5.6 and 9.5; a 1920x1080 mask 9.7 against 5.0 on the GPU. Above it, blocks of
-// kWordsPerBlock words: the adds of all blocks meet at one cache line, and 64 of them cost less
-// than 1024 (3840x2160: 5.9 us, with a block per 256 words 28 us, and with an add for every wave
-// besides 101 us).
+// One block, one launch up to kOneBlockWords: a VGA mask 3.5 us on the GPU and 4.0 us a call from
+// Python, where clearing and counting in many blocks takes 4.7 and 6.6 us; 10^6 pixels 5.9 and 4.1
+// against 4.9 and 6.6, a call in a loop being bound by the launches; a 1920x1080 mask 9.6 against 4.9
+// on the GPU. Above it, blocks of kWordsPerBlock words: the adds of all blocks meet at one cache line,
+// and 64 of them cost less than 1024 (3840x2160: 5.8 us, with a block per 256 words 28 us, and with an
+// add for every wave besides 101 us).
 constexpr uint64_t kOneBlockWords = 16384;
 constexpr uint64_t kWordsPerBlock = 4096;
 
