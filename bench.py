@@ -771,10 +771,10 @@ def bench_plain(args) -> int:
                    "launch": args.mode, "rho": args.rho, "variant": args.variant},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     # rows stream (cache policy 2) if a frame goes through 256 MiB or more of rows, frames
+                     # rows stream (cache policy 2) if a frame goes through 184 MiB or more of rows, frames
                      # and flags (46 bytes a paired pixel, 33 a four-channel one), else they are kept (0)
                      "kernel": f"rgbd::frame_kernel<5, float, {8 if augmented else 7}, "
-                               f"{2 if seg.npix * (33 if augmented else 46) >= 256 << 20 else 0}>",
+                               f"{2 if seg.npix * (33 if augmented else 46) >= 184 << 20 else 0}>",
                      "algorithmic_bytes_per_launch": alg_bytes,
                      "full_rewrite_bytes_per_launch": None if augmented else sorted_bytes,
                      "full_rewrite_frac": None if augmented else sorted_bytes / (ms_step / 1e3) / 1e9 / HBM_PEAK_GBS,

@@ -6,10 +6,10 @@
 // a transfer before the kernel and a submission per frame. A wave's 192 colour bytes and 128 depth
 // bytes are contiguous; such reads reach 57 GB/s over the host link, the rate of one large DMA copy
 // (per-frame DMA copies reach 47), and the kernel's arithmetic hides behind them. A tick of 16 streams (27 MB
-// of frames) took 841 us with copies to the device and back and takes 547 us; one 640x480 stream
-// 127 and 59 us.
-// Frames that are not page-locked, or not aligned for the kernel's loads, are copied to the
-// stream's device slot first (spread over four copy-in streams, so several DMA engines share the
+// of frames) took 843 us with copies to the device and back and takes 541 us; one 640x480 stream
+// 123 and 53 us.
+// Frames that are not page-locked, coherent and in one allocation, or not aligned for the kernel's
+// loads, are copied to the stream's device slot first (spread over four copy-in streams, so several DMA engines share the
 // host link), and such masks go through a device arena and a copy back: the pipeline of the paper's
 // Fig. 4(a), in which the copies of tick N+1 overlap the kernel of tick N and the copy back of
 // tick N-1. A ring of `ring` tick slots bounds the work in flight; a completion thread waits on

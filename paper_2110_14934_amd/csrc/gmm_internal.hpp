@@ -171,12 +171,15 @@ size_t state_bytes(const gmm_handle* h);
 // only if less than that has gone through it since: what counts is the hot bytes of all launches on
 // the device between two frames of a stream, its own included, however they are divided into
 // streams, batches and ticks. A stream's first frame counts its launch alone. The launch takes the
-// policy that is right for the larger part of its bytes. Rows kept against rows streamed, us a call:
-// one batch of VGA fp32 streams, 12 (170 MB) 47.5 and 54.9, 16 (226 MB) 68.8 and 72.2, 24 (339 MB)
-// 109.0 and 105.6; single 1920x1080 fp32 streams in turn, 2 (191 MB) 27.5 and 28.3, 3 (286 MB) 28.5
-// and 28.8, 4 (382 MB) 33.0 and 28.9; 64 VGA streams in turn 8.9 and 7.7; batches of 8 VGA streams in turn,
-// 2 (226 MB) 37.2 and 38.8, 3 (339 MB) 41.1 and 39.4, 4 45.6 and 39.6; 64 VGA fp16 streams in turn
-// 9.4 and 8.0.
-constexpr size_t kStreamHotBytes = size_t(256) << 20;
+// policy that is right for the larger part of its bytes. The line lies below the cache's size, since
+// masks and the suffixes of some pixels go through it too. Rows kept against rows streamed, us a call,
+// every stream with frames of its own: a 2560x1600 paired fp32 stream (188 MB) 51.7 and 53.2, 2400x1800
+// (199 MB) 57.2 and 56.1, 2560x1920 (226 MB) 67.2 and 63.5; one batch of VGA fp32 streams, 12 (170 MB)
+// 54.7 and 56.4, 14 (198 MB) 68.2 and 65.4, 16 (226 MB) 77.9 and 73.0, of 16 fp16 ones (206 MB) 73.1 and
+// 67.5; single streams in turn, two of 1920x1080 (191 MB) 28.7 and 29.0, five of 1280x720 (212 MB) 15.5
+// and 15.2, 13 VGA (184 MB) 7.6 and 7.7, 18 (254 MB) 8.0 and 7.7; batches in turn, two of 7 VGA streams
+// (198 MB) 34.5 and 35.8, two of 8 (226 MB) 39.7 and 39.1, two of 9 fp16 ones (232 MB) 41.4 and 39.7. Far
+// beyond it: eight 1920x1080 fp32 streams in turn 34.4 and 29.1.
+constexpr size_t kStreamHotBytes = size_t(184) << 20;
 bool streams_rows(gmm_handle* const* h, size_t n);
 }  // namespace rgbd

@@ -478,8 +478,9 @@ static void residency() {
   check(1024, 1024, GMM_RGB | GMM_DEPTH, {1, 2}, 2);
 }
 
-// Rows are kept in the 256 MB last-level cache if they are still there when the stream's next frame
-// comes: what other launches on the device go through in between counts, whatever they belong to.
+// Rows are kept in the last-level cache if they are still there when the stream's next frame comes
+// (less than 184 MiB has gone through it): what other launches on the device go through in between
+// counts, whatever they belong to.
 static void cache_policy() {
   constexpr int W = 640, H = 480;  // 307200 pixels, 46 hot bytes each: 14.1 MB
   void* mem = nullptr;
@@ -494,11 +495,11 @@ static void cache_policy() {
     OK(gmm_apply_frame(g, d, 3 * W, reinterpret_cast<uint16_t*>(d), 2 * W, m, m + 4800, nullptr));
     return policy();
   };
-  // single streams: 16 in turn stay in the cache (226 MB), 24 do not, one of them alone does again
-  for (int i = 0; i < 32; ++i) EXPECT(frame(h[i % 16]) == 0);
+  // single streams: 13 in turn stay in the cache (184 MB), 24 do not, one of them alone does again
+  for (int i = 0; i < 26; ++i) EXPECT(frame(h[i % 13]) == 0);
   for (int i = 0; i < 72; ++i) EXPECT(frame(h[i % 24]) == 2 || i < 24);
   for (int i = 0; i < 4; ++i) EXPECT(frame(h[23]) == 0);
-  // one batch of 16, of 24; two of 8 in turn, four of 8 in turn, by either batched call
+  // one batch of 13, of 14; two of 6 in turn, four of 8 in turn, by either batched call
   const auto batches = [&](int count, int each, bool fixed) {
     std::vector<gmm_batch*> b(count);
     int last = -1;
@@ -513,9 +514,9 @@ static void cache_policy() {
     return last;
   };
   for (bool fixed : {false, true}) {
-    EXPECT(batches(1, 16, fixed) == 0);
-    EXPECT(batches(1, 24, fixed) == 2);
-    EXPECT(batches(2, 8, fixed) == 0);
+    EXPECT(batches(1, 13, fixed) == 0);
+    EXPECT(batches(1, 14, fixed) == 2);
+    EXPECT(batches(2, 6, fixed) == 0);
     EXPECT(batches(4, 8, fixed) == 2);
   }
   // a frame of a stream larger than the cache, between two frames of a small one, makes the small one's
