@@ -284,7 +284,10 @@ gmm_status gmm_batch_set_frames(gmm_batch* b, int32_t slot, const gmm_stream_io*
  * Advance every stream of the batch one frame using the frames and masks of slot `slot`, in one
  * launch on `stream`. Per stream, results (masks and state) are bit-identical to
  * gmm_apply_frame (or gmm_apply_frame_fused when `fused` was given). Allocates nothing and does
- * not synchronise: safe to capture in a hipGraph.
+ * not synchronise: safe to capture in a hipGraph. Whether a launch keeps its rows in the caches follows
+ * what the device's launches have gone through since its streams' last frame (results do not depend on
+ * it); a captured launch keeps the choice of its capture, so graphs that will take turns are best
+ * captured after eager launches that did.
  */
 gmm_status gmm_batch_run(gmm_batch* b, int32_t slot, void* stream);
 

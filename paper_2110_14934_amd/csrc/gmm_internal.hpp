@@ -170,8 +170,9 @@ size_t state_bytes(const gmm_handle* h);
 // notes the launch. Rows kept in the last-level cache (256 MB) are there for a stream's next frame
 // only if less than that has gone through it since: what counts is the hot bytes of all launches on
 // the device between two frames of a stream, its own included, however they are divided into
-// streams, batches and ticks. A stream's first frame counts its launch alone. The launch takes the
-// policy that is right for the larger part of its bytes. The line lies below the cache's size, since
+// streams, batches and ticks. A stream's first frame counts its launch alone, and a captured launch
+// keeps the policy of its capture (its replays are not seen). The launch takes the policy that is right
+// for the larger part of its bytes. The line lies below the cache's size, since
 // masks and the suffixes of some pixels go through it too. Rows kept against rows streamed, us a call,
 // every stream with frames of its own: a 2560x1600 paired fp32 stream (188 MB) 51.7 and 53.2, 2400x1800
 // (199 MB) 57.2 and 56.1, 2560x1920 (226 MB) 67.2 and 63.5; one batch of VGA fp32 streams, 12 (170 MB)
